@@ -31,6 +31,7 @@ from paper_2004_02833_amd import autograd as pm_autograd
 PREC = {"fp64": pm.PM_FP64, "fp32": pm.PM_FP32, "bf16": pm.PM_BF16}
 STORE = {"fp64": torch.float64, "fp32": torch.float32, "bf16": torch.bfloat16}
 BYTES = {"fp64": 8, "fp32": 4, "bf16": 2}
+_streams = []  # the program's one stream: passes on one context follow each other
 NOISE = 8      # planes of higher-moment noise, taken in turn by the moments
 CHUNK = 32     # moments read back at a time
 
@@ -184,6 +185,12 @@ def _fit_inputs(case, seed):
     return sa + 1e-3, ss + 1e-3, target, p0
 
 
+def _stream():
+    if not _streams:
+        _streams.append(torch.cuda.Stream())
+    return _streams[0]
+
+
 def _g(case):
     return [case["asym"] ** l for l in range(1, case["N"] + 1)] if case["asym"] else None
 
@@ -196,10 +203,10 @@ def prepare(case, seed):
         pm.pm_set_scattering(None)
         spec = {"N": case["N"], "dx": h, "dt": dt, "nsteps": case["steps"], "checkpoint": case["checkpoint"],
                 "precision": PREC[case["prec"]], "moments": lambda i: host0 if i == 0 else zero}
-        return {"case": case, "sa": sa, "ss": ss, "target": target, "spec": spec, "stream": torch.cuda.Stream()}
+        return {"case": case, "sa": sa, "ss": ss, "target": target, "spec": spec, "stream": _stream()}
     sa, ss, q = _medium(case, 1)
     V = (case["N"] + 1) ** 2
-    state = {"case": case, "V": V, "init": _initial(case, seed), "stream": torch.cuda.Stream(),
+    state = {"case": case, "V": V, "init": _initial(case, seed), "stream": _stream(),
              "out": torch.empty((V,) + _shape(case), dtype=STORE[case["prec"]], device="cuda")}
     if case["prec"] != "fp64":
         state["stage"] = torch.empty((min(V, CHUNK),) + _shape(case), dtype=torch.float64, device="cuda")
