@@ -73,6 +73,10 @@ struct Ctx {
     void* adj_mem = nullptr;  // streams of the transposed sweeps when their depth differs
     pm::WinArgs win[2]{};     // forward sweeps
     pm::WinArgs wadj[2]{};    // transposed sweeps (pm_grad)
+    bool tiled = false;       // forward sweeps run as tile sweeps
+    pm::TileGeom tg{};
+    pm::TileArgs tile[2]{};
+    void* tile_mem = nullptr;
     double* plane64 = nullptr;
     double* red = nullptr;
     unsigned long long* redc = nullptr;
@@ -91,6 +95,7 @@ struct Ctx {
     size_t state_bytes() const { return (size_t)V * (size_t)g.pstride * esz; }
     // element offset of the first plane of a parity within a state
     long long half(int parity) const { return parity ? ve * g.pstride : 0; }
+    int passes(int parity) const { return tiled ? tile[parity].npass : win[parity].npass; }
     hipStream_t stream() const { return g_bound ? g_bound : own; }
     void* plane(void* base, int slot) const {
         return (char*)base + (size_t)slot * (size_t)g.pstride * esz;
@@ -148,6 +153,7 @@ void release() {
     dfree(C.sig);
     dfree(C.gl);
     dfree(C.win_mem);
+    dfree(C.tile_mem);
     dfree(C.halo_slots[0]);
     dfree(C.halo_slots[1]);
     dfree(C.adj_mem);
@@ -294,10 +300,106 @@ int build_window_tables(int K, pm::WinArgs (&win)[2], void** mem) {
     return PM_OK;
 }
 
+// Streams of the tile sweep (layout documented in kernels.h), one depth per
+// parity; the couplings are counted as for the window streams.
+int build_tile_tables() {
+    const pm::Layout& L = C.L;
+    const int N = C.N, V = C.V, MU1 = N + 2;
+    std::unordered_map<long long, double> flux;
+    long long nnz_par[2] = {0, 0};
+    for (const pm::FluxEntry& e : pm::flux_entries(N)) {
+        flux[((long long)e.row * V + e.col) * 3 + e.dir] = e.val;
+        int l, m;
+        pm::moment_lm(e.row, l, m);
+        ++nnz_par[l & 1];
+    }
+    auto exists = [&](int l, int mu, int ty) { return l >= 0 && l <= N && mu >= 0 && mu <= l && !(ty == 1 && mu == 0); };
+    auto idx = [](int l, int mu, int ty) { return l * l + l + (ty == 0 ? mu : -mu); };
+    std::vector<uint32_t> src[2], tgt[2];
+    const long long unit = C.g.pstride / 64;  // entries count 64 elements
+    std::vector<double> coef[2];
+    for (int p = 0; p < 2; ++p) {
+        const int nd = N >= p ? (N - p) / 2 + 1 : 0;
+        const int K = pm::tile_depth(C.prec, nd), npass = (nd + K - 1) / K;
+        C.tile[p] = pm::TileArgs{N, p, K, npass, nullptr, nullptr, nullptr};
+        src[p].assign((size_t)npass * MU1 * 2 * (K + 1), 0);
+        tgt[p].assign((size_t)npass * MU1 * 2 * K, 0);
+        coef[p].assign((size_t)npass * MU1 * 2 * (K + 1) * 10, 0.0);
+        long long used = 0;
+        for (int pass = 0; pass < npass; ++pass) {
+            const int L0 = p + 2 * K * pass;
+            for (int mu = 0; mu < MU1; ++mu)
+                for (int ty = 0; ty < 2; ++ty) {
+                    const size_t col = ((size_t)pass * MU1 + mu) * 2 + ty;
+                    for (int t = 0; t < K; ++t)
+                        if (exists(L0 + 2 * t, mu, ty))
+                            tgt[p][col * K + t] = (uint32_t)((L.slot_of[idx(L0 + 2 * t, mu, ty)] - (p ? (int)C.ve : 0)) * unit);
+                    for (int b = 0; b <= K; ++b) {
+                        const int ls = L0 - 1 + 2 * b;
+                        if (!exists(ls, mu, ty)) continue;
+                        const int j = idx(ls, mu, ty);
+                        const int bits = pm::grid_bits(ls, ty == 0 ? mu : -mu);
+                        src[p][col * (K + 1) + b] = (uint32_t)((L.slot_of[j] - (p ? 0 : (int)C.ve)) * unit);
+                        for (int side = 0; side < 2; ++side) {
+                            const int t = side == 0 ? b : b - 1;
+                            if (t < 0 || t >= K) continue;
+                            const int tmu[5] = {mu - 1, mu - 1, mu, mu + 1, mu + 1};
+                            const int tty[5] = {ty, 1 - ty, ty, ty, 1 - ty};
+                            const int dir[5] = {0, 1, 2, 0, 1};
+                            for (int r = 0; r < 5; ++r) {
+                                if (!exists(L0 + 2 * t, tmu[r], tty[r])) continue;
+                                auto it = flux.find(((long long)idx(L0 + 2 * t, tmu[r], tty[r]) * V + j) * 3 + dir[r]);
+                                if (it == flux.end()) continue;
+                                const double sgn = ((bits >> dir[r]) & 1) ? -1.0 : 1.0;
+                                coef[p][((col * (K + 1) + b) * 2 + side) * 5 + r] = sgn * it->second / C.h[dir[r]];
+                                ++used;
+                            }
+                        }
+                    }
+                }
+        }
+        if (used != nnz_par[p])
+            return fail(PM_EINVAL, "internal: tile streams cover " + std::to_string(used) + " of " +
+                                       std::to_string(nnz_par[p]) + " couplings");
+        const long long nhalf[2] = {C.ve, (long long)V - C.ve};
+        for (uint32_t e : src[p])
+            if (e >= nhalf[1 - p] * unit) return fail(PM_EINVAL, "internal: source slot outside its half");
+        for (uint32_t e : tgt[p])
+            if (e >= nhalf[p] * unit) return fail(PM_EINVAL, "internal: target slot outside its half");
+    }
+    const bool f64 = C.prec == PM_FP64;
+    const size_t es = f64 ? sizeof(double) : sizeof(float);
+    auto up = [](size_t x) { return (x + 255) / 256 * 256; };
+    std::vector<char> host;
+    size_t off[2][3];
+    auto put = [&](const void* p, size_t bytes) {
+        const size_t at = host.size();
+        host.resize(at + up(bytes));
+        if (bytes) std::memcpy(host.data() + at, p, bytes);
+        return at;
+    };
+    for (int p = 0; p < 2; ++p) {
+        off[p][0] = put(src[p].data(), src[p].size() * sizeof(int));
+        off[p][1] = put(tgt[p].data(), tgt[p].size() * sizeof(int));
+        std::vector<float> c32(coef[p].begin(), coef[p].end());
+        off[p][2] = f64 ? put(coef[p].data(), coef[p].size() * es) : put(c32.data(), c32.size() * es);
+    }
+    int rc = dmalloc(&C.tile_mem, host.size(), "tile streams");
+    if (rc) return rc;
+    HIPCHK(hipMemcpy(C.tile_mem, host.data(), host.size(), hipMemcpyHostToDevice));
+    for (int p = 0; p < 2; ++p) {
+        char* base = (char*)C.tile_mem;
+        C.tile[p].src = (const uint32_t*)(base + off[p][0]);
+        C.tile[p].tgt = (const uint32_t*)(base + off[p][1]);
+        C.tile[p].coef = base + off[p][2];
+    }
+    return PM_OK;
+}
+
 // One sweep of the given parity; `full` selects tau = dt for the odd grids
 // (two merged odd half steps).
 int sweep(void* u, int parity, bool full = false) {
-    if (C.win[parity].npass == 0) return PM_OK;
+    if (C.passes(parity) == 0) return PM_OK;
     hipEvent_t a = nullptr, b = nullptr;
     if (C.timing) {
         HIPCHK(hipEventCreate(&a));
@@ -308,7 +410,10 @@ int sweep(void* u, int parity, bool full = false) {
     const int rowbase = parity == 0 ? 0 : full && !C.aniso ? pm::kTabOddFull : 8;
     const pm::Aniso an{C.aniso ? C.gl : nullptr, tau};
     const pm::StateOffs so{C.half(1 - parity), C.half(parity), C.half(parity), 0, 0};
-    HIPCHK(pm::launch_sweep_win(C.prec, u, so, C.tab, C.tabf, rowbase, an, C.win[parity], C.g, C.stream()));
+    if (C.tiled)
+        HIPCHK(pm::launch_sweep_tile(C.prec, u, so, C.tab, C.tabf, rowbase, C.tile[parity], C.tg, C.g, C.stream()));
+    else
+        HIPCHK(pm::launch_sweep_win(C.prec, u, so, C.tab, C.tabf, rowbase, an, C.win[parity], C.g, C.stream()));
     if (C.timing) {
         HIPCHK(hipEventRecord(b, C.stream()));
         C.ev[parity].push_back({a, b});
@@ -518,9 +623,12 @@ int pm_init_cells(int N, int nx, int ny, int nz, double dx, double dy, double dz
     TRY(dmalloc(&C.red, sizeof(double) * (std::max(C.npart, C.ncheck) + 1), "reduction"));
     TRY(dmalloc(&C.redc, sizeof(unsigned long long) * (C.ncheck + 1), "reduction"));
     const int kwin = pm::win_depth(C.prec, nx, N, C.aniso);
-    TRY(build_window_tables(kwin, C.win, &C.win_mem));
-
-    if (C.prec != PM_BF16 && pm::adj_depth(C.prec) != kwin) {
+    C.tiled = !C.aniso && pm::tile_use(C.prec, N, C.g, C.tg);
+    if (C.tiled)
+        TRY(build_tile_tables());
+    else
+        TRY(build_window_tables(kwin, C.win, &C.win_mem));
+    if (C.prec != PM_BF16 && (C.tiled || pm::adj_depth(C.prec) != kwin)) {
         TRY(build_window_tables(pm::adj_depth(C.prec), C.wadj, &C.adj_mem));
     } else {
         C.wadj[0] = C.win[0];
@@ -737,10 +845,12 @@ int grad_impl(const double* dL_du0, double* dsa, double* dss, bool dev) {
     double* gp_par[2] = {gpass, gpass + (size_t)np0 * pm::kGradRows * (size_t)n};
     C.timing = false;
     auto fwd = [&](int p, long long src, long long tin, long long tout) -> hipError_t {
-        if (C.win[p].npass == 0) return hipSuccess;  // a parity without moments (N = 0, odd)
+        if (C.passes(p) == 0) return hipSuccess;  // a parity without moments (N = 0, odd)
         const pm::Aniso an{C.aniso ? C.gl : nullptr, p ? 0.5 * C.dt : C.dt};
-        return pm::launch_sweep_win(C.prec, pool, pm::StateOffs{src, tin, tout, 0, 0}, C.tab, C.tabf,
-                                    p ? 8 : 0, an, C.win[p], C.g, s);
+        const pm::StateOffs so{src, tin, tout, 0, 0};
+        if (C.tiled)
+            return pm::launch_sweep_tile(C.prec, pool, so, C.tab, C.tabf, p ? 8 : 0, C.tile[p], C.tg, C.g, s);
+        return pm::launch_sweep_win(C.prec, pool, so, C.tab, C.tabf, p ? 8 : 0, an, C.win[p], C.g, s);
     };
     // transpose of the substep of parity p whose old state has halves (E, O)
     auto adj = [&](int p, long long E, long long O) -> hipError_t {

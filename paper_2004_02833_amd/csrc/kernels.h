@@ -95,6 +95,37 @@ struct StateOffs {
 hipError_t launch_sweep_win(int prec, void* pool, StateOffs so, const double* tab, const float* tabf,
                             int rowbase, Aniso an, WinArgs a, GridDesc g, hipStream_t st);
 
+// Tile sweep (see sweep_tile.hip): boxes of w x ty x tz cells, one per
+// workgroup, nseg x nty x ntz of them; a row image takes rowch 16-byte
+// chunks, the first nmain of them the row's own cells; whole: a box holds
+// whole rows.  bx x by x bz boxes form a block that stays on one XCD.
+struct TileGeom {
+    int w, ty, tz;
+    int nseg, nty, ntz;
+    int rowch, nmain;
+    int whole;
+    int bx, by, bz;
+};
+// Host-built streams of the tile sweep, for pass p, column mu = 0..N + 1,
+// type ty (0 cos, 1 sin):
+//   src[((p * MU1 + mu) * 2 + ty) * (K + 1) + b]  plane of degree L0 - 1 + 2b
+//   tgt[((p * MU1 + mu) * 2 + ty) * K + t]        plane of degree L0 + 2t
+//   coef[((((p * MU1 + mu) * 2 + ty) * (K + 1) + b) * 2 + side) * 5 + r]
+// (0 where it does not exist), MU1 = N + 2, the roles r and the sides as in
+// the window streams; planes as offsets from the first plane of their
+// parity in units of 64 elements.
+struct TileArgs {
+    int N, parity, K, npass;
+    const uint32_t* src;
+    const uint32_t* tgt;
+    const void* coef;
+};
+bool tile_use(int prec, int N, const GridDesc& g, TileGeom& tg);  // and fills tg
+int tile_depth(int prec, int nd);
+hipError_t launch_sweep_tile(int prec, void* pool, StateOffs so, const double* tab, const float* tabf,
+                             int rowbase, const TileArgs& a, const TileGeom& tg, const GridDesc& g,
+                             hipStream_t st);
+
 // Transposed substep on the window streams.  side 0 (target side): so.src /
 // so.aux = dual / target half of the old state, tin = tout = cotangent lam
 // of the targets (updated), w = output beta * lam, gp = per-pass gradient

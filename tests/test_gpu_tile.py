@@ -1,0 +1,65 @@
+"""The tile sweep against the C oracle at the edges of its boxes: rows of
+whole lines, rows that start inside a cache line or a 16-byte chunk, rows cut
+into segments with a short last one, boxes hanging over the grid in y and z,
+planes and slabs, one and several passes with an empty last source degree,
+and moment 0 with its source in the first even pass.
+
+FP64: a step rounds each of at most ten couplings per moment, so 2 steps stay
+below 1e-13 of the largest value; FP32: 2^-24 per rounding of the same count,
+below 1e-6 over 2 steps."""
+import numpy as np
+import pytest
+
+import paper_2004_02833_amd as pm
+from oracle import c_oracle
+
+from gpu_util import gpu_run, relerr, say
+
+pytestmark = pytest.mark.gpu
+
+# (N, nx, ny, nz): every one has enough boxes for the tile sweep
+FP64 = [(3, 64, 66, 62), (3, 63, 65, 70), (3, 100, 75, 40), (5, 161, 45, 33), (3, 250, 1201, 1),
+        (3, 2, 300, 410), (4, 17, 95, 101), (7, 33, 90, 61), (9, 80, 41, 27), (12, 48, 45, 41)]
+FP32 = [(4, 64, 92, 92), (4, 250, 61, 36), (5, 33, 130, 111), (4, 160, 67, 62), (5, 130, 3200, 1),
+        (9, 96, 75, 56), (11, 77, 52, 61), (14, 20, 130, 97)]
+
+
+def _run(N, shape, prec, tol):
+    nz, ny, nx = shape
+    rng = np.random.default_rng(1000 * N + nx)
+    V = (N + 1) ** 2
+    h = 1.0 / max(shape)
+    sa, ss, q = rng.uniform(0, 2, shape), rng.uniform(0, 2, shape), rng.uniform(0, 1, shape)
+    u0 = rng.standard_normal((V,) + shape)
+    if prec == pm.PM_FP32:
+        u0 = u0.astype(np.float32).astype(np.float64)
+    ref = c_oracle.run(N, shape, h, 0.5 * h, sa, ss, q, u0, 2)
+    got = gpu_run(N, shape, h, 0.5 * h, sa, ss, q, u0, 2, prec=prec)
+    e = relerr(got, ref)
+    say("tile P%d %dx%dx%d prec %d: %.2e" % (N, nx, ny, nz, prec, e))
+    assert e <= tol
+
+
+@pytest.mark.parametrize("N,nx,ny,nz", FP64)
+def test_tile_fp64(N, nx, ny, nz):
+    _run(N, (nz, ny, nx), pm.PM_FP64, 1e-13)
+
+
+@pytest.mark.parametrize("N,nx,ny,nz", FP32)
+def test_tile_fp32(N, nx, ny, nz):
+    _run(N, (nz, ny, nx), pm.PM_FP32, 1e-6)
+
+
+def test_tile_nonfinite_values_stay_local():
+    """An infinity reaches only the moments and cells coupled to it: empty
+    source slots and idle lanes contribute nothing."""
+    N, shape = 4, (40, 50, 130)
+    V = 25
+    one = np.ones(shape)
+    u0 = np.zeros((V,) + shape)
+    u0[6, 20, 25, 64] = np.inf
+    got = gpu_run(N, shape, 1 / 64, 0.5 / 64, one, one, None, u0, 1)
+    bad = ~np.isfinite(got)
+    assert bad[6, 20, 25, 64]
+    z, y, x = np.nonzero(bad.any(axis=0))
+    assert max(abs(z - 20).max(), abs(y - 25).max(), abs(x - 64).max()) <= 3
