@@ -13,7 +13,6 @@
 #include <cstdio>
 #include <cstring>
 #include <string>
-#include <unordered_map>
 #include <utility>
 #include <vector>
 
@@ -75,8 +74,8 @@ struct Ctx {
     pm::WinArgs wadj[2]{};    // transposed sweeps (pm_grad)
     bool tiled = false;       // forward sweeps run as tile sweeps
     pm::TileGeom tg{};
-    pm::TileArgs tile[2]{};
-    void* tile_mem = nullptr;
+    pm::TileArgs tile[2]{}, tadj[2]{};  // forward and transposed
+    void* tile_mem[2] = {nullptr, nullptr};
     double* plane64 = nullptr;
     double* red = nullptr;
     unsigned long long* redc = nullptr;
@@ -153,7 +152,8 @@ void release() {
     dfree(C.sig);
     dfree(C.gl);
     dfree(C.win_mem);
-    dfree(C.tile_mem);
+    dfree(C.tile_mem[0]);
+    dfree(C.tile_mem[1]);
     dfree(C.halo_slots[0]);
     dfree(C.halo_slots[1]);
     dfree(C.adj_mem);
@@ -181,6 +181,28 @@ long long plane_stride(long long ncell) {
     return s;
 }
 
+// The flux entries by target row (at most ten each).
+struct FluxRows {
+    std::vector<pm::FluxEntry> e;
+    std::vector<int> begin;
+    long long nnz_par[2] = {0, 0};  // entries with targets of a parity
+
+    explicit FluxRows(int N) : begin((size_t)(N + 1) * (N + 1) + 1, 0) {
+        const std::vector<pm::FluxEntry> all = pm::flux_entries(N);
+        for (const pm::FluxEntry& f : all) ++begin[f.row + 1];
+        for (size_t i = 1; i < begin.size(); ++i) begin[i] += begin[i - 1];
+        e.resize(all.size());
+        std::vector<int> at(begin.begin(), begin.end() - 1);
+        for (const pm::FluxEntry& f : all) e[at[f.row]++] = f;
+        for (int l = 0; l <= N; ++l) nnz_par[l & 1] += begin[(size_t)(l + 1) * (l + 1)] - begin[(size_t)l * l];
+    }
+    const double* find(int row, int col, int dir) const {
+        for (int k = begin[row]; k < begin[row + 1]; ++k)
+            if (e[k].col == col && e[k].dir == dir) return &e[k].val;
+        return nullptr;
+    }
+};
+
 // Streams of the window sweep (layout documented in kernels.h).  Every
 // nonzero flux entry with a target of the sweep's parity must land in exactly
 // one coefficient slot; the count is checked.
@@ -189,14 +211,8 @@ int build_window_tables(int K, pm::WinArgs (&win)[2], void** mem) {
     // columns mu = 0..N+1 and one empty column N+2: a sweep requests the next
     // column's sources unconditionally
     const int N = C.N, V = C.V, MU1 = N + 3;
-    std::unordered_map<long long, double> flux;
-    long long nnz_par[2] = {0, 0};
-    for (const pm::FluxEntry& e : pm::flux_entries(N)) {
-        flux[((long long)e.row * V + e.col) * 3 + e.dir] = e.val;
-        int l, m;
-        pm::moment_lm(e.row, l, m);
-        ++nnz_par[l & 1];
-    }
+    const FluxRows flux(N);
+    const long long* nnz_par = flux.nnz_par;
     auto exists = [&](int l, int mu, int ty) {
         return l >= 0 && l <= N && mu >= 0 && mu <= l && !(ty == 1 && mu == 0);
     };
@@ -238,11 +254,11 @@ int build_window_tables(int K, pm::WinArgs (&win)[2], void** mem) {
                             for (int r = 0; r < 5; ++r) {
                                 if (!exists(lt, tmu[r], tty[r])) continue;
                                 const int i = idx(lt, tmu[r], tty[r]);
-                                auto it = flux.find(((long long)i * V + j) * 3 + dir[r]);
-                                if (it == flux.end()) continue;
+                                const double* val = flux.find(i, j, dir[r]);
+                                if (!val) continue;
                                 const double sgn = ((bits >> dir[r]) & 1) ? -1.0 : 1.0;
                                 h.coef[((((size_t)(pass * MU1 + mu) * (K + 1) + b) * 2 + ty) * 2 + side) * 5 + r] =
-                                    sgn * it->second / C.h[dir[r]];
+                                    sgn * *val / C.h[dir[r]];
                                 ++used;
                             }
                         }
@@ -300,19 +316,13 @@ int build_window_tables(int K, pm::WinArgs (&win)[2], void** mem) {
     return PM_OK;
 }
 
-// Streams of the tile sweep (layout documented in kernels.h), one depth per
-// parity; the couplings are counted as for the window streams.
-int build_tile_tables() {
+// Streams of the forward or transposed tile sweep (layout documented in
+// kernels.h), one depth per parity; the couplings are counted as for the window streams.
+int build_tile_tables(bool adj, pm::TileArgs (&tile)[2], void** mem) {
     const pm::Layout& L = C.L;
     const int N = C.N, V = C.V, MU1 = N + 2;
-    std::unordered_map<long long, double> flux;
-    long long nnz_par[2] = {0, 0};
-    for (const pm::FluxEntry& e : pm::flux_entries(N)) {
-        flux[((long long)e.row * V + e.col) * 3 + e.dir] = e.val;
-        int l, m;
-        pm::moment_lm(e.row, l, m);
-        ++nnz_par[l & 1];
-    }
+    const FluxRows flux(N);
+    const long long* nnz_par = flux.nnz_par;
     auto exists = [&](int l, int mu, int ty) { return l >= 0 && l <= N && mu >= 0 && mu <= l && !(ty == 1 && mu == 0); };
     auto idx = [](int l, int mu, int ty) { return l * l + l + (ty == 0 ? mu : -mu); };
     std::vector<uint32_t> src[2], tgt[2];
@@ -320,8 +330,8 @@ int build_tile_tables() {
     std::vector<double> coef[2];
     for (int p = 0; p < 2; ++p) {
         const int nd = N >= p ? (N - p) / 2 + 1 : 0;
-        const int K = pm::tile_depth(C.prec, nd), npass = (nd + K - 1) / K;
-        C.tile[p] = pm::TileArgs{N, p, K, npass, nullptr, nullptr, nullptr};
+        const int K = pm::tile_depth(C.prec, nd, adj), npass = (nd + K - 1) / K;
+        tile[p] = pm::TileArgs{N, p, K, npass, nullptr, nullptr, nullptr};
         src[p].assign((size_t)npass * MU1 * 2 * (K + 1), 0);
         tgt[p].assign((size_t)npass * MU1 * 2 * K, 0);
         coef[p].assign((size_t)npass * MU1 * 2 * (K + 1) * 10, 0.0);
@@ -348,10 +358,10 @@ int build_tile_tables() {
                             const int dir[5] = {0, 1, 2, 0, 1};
                             for (int r = 0; r < 5; ++r) {
                                 if (!exists(L0 + 2 * t, tmu[r], tty[r])) continue;
-                                auto it = flux.find(((long long)idx(L0 + 2 * t, tmu[r], tty[r]) * V + j) * 3 + dir[r]);
-                                if (it == flux.end()) continue;
+                                const double* val = flux.find(idx(L0 + 2 * t, tmu[r], tty[r]), j, dir[r]);
+                                if (!val) continue;
                                 const double sgn = ((bits >> dir[r]) & 1) ? -1.0 : 1.0;
-                                coef[p][((col * (K + 1) + b) * 2 + side) * 5 + r] = sgn * it->second / C.h[dir[r]];
+                                coef[p][((col * (K + 1) + b) * 2 + side) * 5 + r] = sgn * *val / C.h[dir[r]];
                                 ++used;
                             }
                         }
@@ -384,14 +394,14 @@ int build_tile_tables() {
         std::vector<float> c32(coef[p].begin(), coef[p].end());
         off[p][2] = f64 ? put(coef[p].data(), coef[p].size() * es) : put(c32.data(), c32.size() * es);
     }
-    int rc = dmalloc(&C.tile_mem, host.size(), "tile streams");
+    int rc = dmalloc(mem, host.size(), "tile streams");
     if (rc) return rc;
-    HIPCHK(hipMemcpy(C.tile_mem, host.data(), host.size(), hipMemcpyHostToDevice));
+    HIPCHK(hipMemcpy(*mem, host.data(), host.size(), hipMemcpyHostToDevice));
     for (int p = 0; p < 2; ++p) {
-        char* base = (char*)C.tile_mem;
-        C.tile[p].src = (const uint32_t*)(base + off[p][0]);
-        C.tile[p].tgt = (const uint32_t*)(base + off[p][1]);
-        C.tile[p].coef = base + off[p][2];
+        char* base = (char*)*mem;
+        tile[p].src = (const uint32_t*)(base + off[p][0]);
+        tile[p].tgt = (const uint32_t*)(base + off[p][1]);
+        tile[p].coef = base + off[p][2];
     }
     return PM_OK;
 }
@@ -408,7 +418,7 @@ int sweep(void* u, int parity, bool full = false) {
     }
     const double tau = parity == 0 || full ? C.dt : 0.5 * C.dt;
     const int rowbase = parity == 0 ? 0 : full && !C.aniso ? pm::kTabOddFull : 8;
-    const pm::Aniso an{C.aniso ? C.gl : nullptr, tau};
+    const pm::Aniso an{C.aniso ? C.gl : nullptr, tau, 0};
     const pm::StateOffs so{C.half(1 - parity), C.half(parity), C.half(parity), 0, 0};
     if (C.tiled)
         HIPCHK(pm::launch_sweep_tile(C.prec, u, so, C.tab, C.tabf, rowbase, C.tile[parity], C.tg, C.g, C.stream()));
@@ -624,11 +634,13 @@ int pm_init_cells(int N, int nx, int ny, int nz, double dx, double dy, double dz
     TRY(dmalloc(&C.redc, sizeof(unsigned long long) * (C.ncheck + 1), "reduction"));
     const int kwin = pm::win_depth(C.prec, nx, N, C.aniso);
     C.tiled = !C.aniso && pm::tile_use(C.prec, N, C.g, C.tg);
-    if (C.tiled)
-        TRY(build_tile_tables());
-    else
+    if (C.tiled) {
+        TRY(build_tile_tables(false, C.tile, &C.tile_mem[0]));
+        TRY(build_tile_tables(true, C.tadj, &C.tile_mem[1]));
+    } else {
         TRY(build_window_tables(kwin, C.win, &C.win_mem));
-    if (C.prec != PM_BF16 && (C.tiled || pm::adj_depth(C.prec) != kwin)) {
+    }
+    if (!C.tiled && C.prec != PM_BF16 && pm::adj_depth(C.prec) != kwin) {
         TRY(build_window_tables(pm::adj_depth(C.prec), C.wadj, &C.adj_mem));
     } else {
         C.wadj[0] = C.win[0];
@@ -759,13 +771,16 @@ int pm_set_checkpoint(int k) {
     return PM_OK;
 }
 
-// Reverse pass.  One pool holds lam, w and the states of a segment as
-// parity halves: a substep writes the new half of its own parity into a fresh
-// buffer and shares the other half with its input, so the recomputation of a
-// segment keeps every intermediate substep state without copies.  For step
-// j of a segment with state (E_j, O_j): O'_j = S^o half step, E'_j = S^e,
-// O''_j = S^o again, and state j + 1 = (E'_j, O''_j).  The transposes then
-// run on (E'_j, O'_j), (E_j, O'_j) and (E_j, O_j).
+// Reverse pass.  The steps run as the merged schedule: the substeps of a run
+// of T steps are O(half) E O E ... O E O(half), every inner O a full odd
+// substep, and the last half step has no cotangent.  Segments between
+// checkpoints are recomputed, last first: from (E_0, O_0) of a checkpoint
+// the odd states P = O'_0 (after its opening half step), O'_1 .. O'_{len-1}
+// and the even states E_1 .. E_len, a substep writing its own half into a
+// fresh buffer.  The transposed substeps (launch_adj_*) need the target's
+// values before and after: (E_j, E_{j+1}) for an even one, (O'_{j-1}, O'_j)
+// for an odd one; the odd substep between two segments runs from the earlier
+// one's last O' to the later one's P, kept in a buffer of its own.
 }  // extern "C"
 
 namespace {
@@ -777,7 +792,6 @@ int grad_impl(const double* dL_du0, double* dsa, double* dss, bool dev) {
     if (C.ck <= 0) return fail(PM_ESTATE, "no gradient recording: call pm_set_checkpoint(k > 0) before pm_step");
     if (!dL_du0) return fail(PM_EINVAL, "dL_du0 is NULL");
     hipStream_t s = C.stream();
-    const size_t SB = C.state_bytes();
     const long long n = C.ncell;
     const long long T = C.rec_steps;
     const int ck = C.ck;
@@ -785,9 +799,8 @@ int grad_impl(const double* dL_du0, double* dsa, double* dss, bool dev) {
     const long long SE = (long long)C.V * ps;      // elements of a state
     const long long EH = C.ve * ps;                 // elements of the even half
     const long long OH = SE - EH;                   // elements of the odd half
-    const long long region = 2 * OH + EH;           // O', E', O'' of one step
     const int segs = T > 0 ? (int)std::min<long long>(ck, T) : 1;
-    const long long pool_elems = 3 * SE + (long long)segs * region;
+    const long long pool_elems = SE + 2 * OH + segs * EH + (segs - 1) * OH;
     void* pool = nullptr;
     double *grad = nullptr, *outg = nullptr, *gpass = nullptr;
     const long long before = C.dev_bytes;
@@ -814,8 +827,10 @@ int grad_impl(const double* dL_du0, double* dsa, double* dss, bool dev) {
             return fail(PM_EDEVICE, std::string(#x) + ": " + hipGetErrorString(e_));   \
         }                                                                              \
     } while (0)
-    const int np0 = C.wadj[0].npass, np1 = C.wadj[1].npass;
-    const size_t gpb = sizeof(double) * pm::kGradRows * (size_t)n;  // one pass of gradient rows
+    const int np0 = C.tiled ? C.tadj[0].npass : C.wadj[0].npass;
+    const int np1 = C.tiled ? C.tadj[1].npass : C.wadj[1].npass;
+    const int rows = pm::grad_rows(C.aniso);
+    const size_t gpb = sizeof(double) * rows * (size_t)n;  // one pass of gradient rows
     const size_t pool_bytes = C.esz * (size_t)pool_elems;
     {
         size_t fr = 0, tot = 0;
@@ -829,67 +844,68 @@ int grad_impl(const double* dL_du0, double* dsa, double* dss, bool dev) {
     TRYG(dmalloc(&gpass, gpb * (size_t)(np0 + np1), "per-pass gradient rows"));
     TRYG(dmalloc(&grad, gpb, "gradient accumulators"));
     TRYG(dmalloc(&outg, sizeof(double) * 2 * (size_t)n, "gradient output"));
-    // pool layout (elements): lam [0, SE), w [SE, 2 SE), segment start state
-    // [2 SE, 3 SE), then one region per step
-    const long long LAM = 0, W = SE, START = 2 * SE;
-    auto reg = [&](long long j) { return 3 * SE + j * region; };
-    auto Ej = [&](long long j) { return j == 0 ? START : reg(j - 1) + OH; };
-    auto Oj = [&](long long j) { return j == 0 ? START + EH : reg(j - 1) + OH + EH; };
-    auto O1 = [&](long long j) { return reg(j); };
-    auto E1 = [&](long long j) { return reg(j) + OH; };
-    auto O2 = [&](long long j) { return reg(j) + OH + EH; };
+    // pool layout (elements): w [0, SE), P of even and odd segments, E_1 ..
+    // E_len, O'_1 .. O'_{len-1}; the checkpoints are read where they are
+    const long long W = 0, P0 = SE, EB = SE + 2 * OH, OB = EB + segs * EH;
     HIPG(pm::launch_fill_zero(pool, (long long)(C.esz * (size_t)SE), s));
     HIPG(pm::launch_fill_zero(gpass, (long long)(gpb * (np0 + np1)), s));
     if (!dev) HIPG(hipMemcpyAsync(C.plane64, dL_du0, sizeof(double) * n, hipMemcpyHostToDevice, s));
-    HIPG(pm::launch_from_f64(C.prec, dev ? dL_du0 : C.plane64, C.plane(pool, C.L.slot_of[0]), n, s));
-    double* gp_par[2] = {gpass, gpass + (size_t)np0 * pm::kGradRows * (size_t)n};
+    double* gp_par[2] = {gpass, gpass + (size_t)np0 * rows * (size_t)n};
     C.timing = false;
-    auto fwd = [&](int p, long long src, long long tin, long long tout) -> hipError_t {
+    auto odd_tau = [&](bool full) { return full ? C.dt : 0.5 * C.dt; };
+    auto odd_row = [&](bool full) { return full && !C.aniso ? pm::kTabOddFull : 8; };
+    auto fwd = [&](int p, long long src, long long tin, long long tout, bool full) -> hipError_t {
         if (C.passes(p) == 0) return hipSuccess;  // a parity without moments (N = 0, odd)
-        const pm::Aniso an{C.aniso ? C.gl : nullptr, p ? 0.5 * C.dt : C.dt};
+        const pm::Aniso an{C.aniso ? C.gl : nullptr, p ? odd_tau(full) : C.dt, 0};
         const pm::StateOffs so{src, tin, tout, 0, 0};
+        const int row = p ? odd_row(full) : 0;
         if (C.tiled)
-            return pm::launch_sweep_tile(C.prec, pool, so, C.tab, C.tabf, p ? 8 : 0, C.tile[p], C.tg, C.g, s);
-        return pm::launch_sweep_win(C.prec, pool, so, C.tab, C.tabf, p ? 8 : 0, an, C.win[p], C.g, s);
+            return pm::launch_sweep_tile(C.prec, pool, so, C.tab, C.tabf, row, C.tile[p], C.tg, C.g, s);
+        return pm::launch_sweep_win(C.prec, pool, so, C.tab, C.tabf, row, an, C.win[p], C.g, s);
     };
-    // transpose of the substep of parity p whose old state has halves (E, O)
-    auto adj = [&](int p, long long E, long long O) -> hipError_t {
-        const pm::Aniso an{C.aniso ? C.gl : nullptr, p ? 0.5 * C.dt : C.dt};
-        const long long lam_t = LAM + (p ? EH : 0), lam_d = LAM + (p ? 0 : EH);
-        const long long w_t = W + (p ? EH : 0);
-        if (C.wadj[p].npass > 0) {
-            const pm::StateOffs so{p ? E : O, lam_t, lam_t, p ? O : E, w_t};
-            hipError_t e = pm::launch_adj_win(C.prec, 0, pool, so, gp_par[p], C.tab, p ? 8 : 0, an,
-                                              C.wadj[p], C.g, s);
-            if (e != hipSuccess) return e;
-        }
-        if (C.wadj[1 - p].npass > 0) {
-            const pm::StateOffs so{w_t, lam_d, lam_d, 0, 0};
-            return pm::launch_adj_win(C.prec, 1, pool, so, nullptr, C.tab, 0, an, C.wadj[1 - p],
-                                      C.g, s);
-        }
-        return hipSuccess;
+    // transpose of a substep of parity p with the target values pre and post
+    auto adj = [&](int p, long long pre, long long post, bool full) -> hipError_t {
+        if ((p ? np1 : np0) == 0) return hipSuccess;
+        const long long we = W, wo = W + EH;
+        const pm::StateOffs so{p ? we : wo, p ? wo : we, p ? wo : we, pre, post};
+        const int row = p ? odd_row(full) : 0, opening = p && !full;
+        const double tau = p ? odd_tau(full) : C.dt;
+        if (C.tiled)
+            return pm::launch_adj_tile(C.prec, pool, so, gp_par[p], C.tab, row, tau, opening, C.tadj[p], C.tg, C.g, s);
+        return pm::launch_adj_win(C.prec, pool, so, gp_par[p], C.tab, row, pm::Aniso{C.aniso ? C.gl : nullptr, tau, opening},
+                                  C.wadj[p], C.g, s);
     };
     const long long nseg = (T + ck - 1) / ck;
     for (long long gseg = nseg - 1; gseg >= 0; --gseg) {
         const long long s0 = gseg * ck, len = std::min<long long>(s0 + ck, T) - s0;
-        HIPG(hipMemcpyAsync((char*)pool + C.esz * START, C.ckpts[gseg], SB, hipMemcpyDeviceToDevice, s));
+        const long long E0 = ((char*)C.ckpts[gseg] - (char*)pool) / (long long)C.esz, O0 = E0 + EH;
+        auto P = [&](long long g) { return P0 + (g & 1) * OH; };
+        auto E = [&](long long j) { return j == 0 ? E0 : EB + (j - 1) * EH; };
+        auto O1 = [&](long long j) { return j == 0 ? P(gseg) : OB + (j - 1) * OH; };
         for (long long j = 0; j < len; ++j) {
-            HIPG(fwd(1, Ej(j), Oj(j), O1(j)));
-            HIPG(fwd(0, O1(j), Ej(j), E1(j)));
-            if (j + 1 < len) HIPG(fwd(1, E1(j), O1(j), O2(j)));
+            HIPG(j == 0 ? fwd(1, E0, O0, O1(0), false) : fwd(1, E(j), O1(j - 1), O1(j), true));
+            HIPG(fwd(0, O1(j), E(j), E(j + 1), false));
         }
-        for (long long j = len - 1; j >= 0; --j) {
-            HIPG(adj(1, E1(j), O1(j)));  // the closing odd half step
-            HIPG(adj(0, Ej(j), O1(j)));  // the even step
-            HIPG(adj(1, Ej(j), Oj(j)));  // the opening odd half step
+        const long long m0 = (long long)C.L.slot_of[0] * ps;
+        auto at = [&](long long off) { return (char*)pool + (long long)C.esz * off; };
+        if (gseg == nseg - 1) {
+            HIPG(pm::launch_adj_seed(C.prec, dev ? dL_du0 : C.plane64, at(W + m0), at(E(len - 1) + m0), at(E(len) + m0), C.tab,
+                                     C.aniso, C.dt, gp_par[0], n, s));
+        } else {
+            HIPG(adj(1, O1(len - 1), P(gseg + 1), true));
+            HIPG(adj(0, E(len - 1), E(len), false));
         }
+        for (long long j = len - 1; j >= 1; --j) {
+            HIPG(adj(1, O1(j - 1), O1(j), true));
+            HIPG(adj(0, E(j - 1), E(j), false));
+        }
+        if (gseg == 0) HIPG(adj(1, O0, O1(0), false));  // the opening half step
     }
-    HIPG(pm::launch_grad_sum(gpass, np0 + np1, grad, n, s));
+    HIPG(pm::launch_grad_sum(gpass, np0 + np1, grad, rows * n, s));
     if (dev) {
-        HIPG(pm::launch_grad_final(grad, C.tab, C.sig, C.sig + n, dsa, dss, C.g, C.dt, C.aniso, s));
+        HIPG(pm::launch_grad_final(grad, dsa, dss, C.g, C.aniso, s));
     } else {
-        HIPG(pm::launch_grad_final(grad, C.tab, C.sig, C.sig + n, outg, outg + n, C.g, C.dt, C.aniso, s));
+        HIPG(pm::launch_grad_final(grad, outg, outg + n, C.g, C.aniso, s));
         if (dsa) HIPG(hipMemcpyAsync(dsa, outg, sizeof(double) * n, hipMemcpyDeviceToHost, s));
         if (dss) HIPG(hipMemcpyAsync(dss, outg + n, sizeof(double) * n, hipMemcpyDeviceToHost, s));
     }

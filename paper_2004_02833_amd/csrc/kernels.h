@@ -17,9 +17,10 @@ constexpr int kTabRows = 27;
 constexpr int kTabMom0 = 16;
 constexpr int kTabQ = 18;
 constexpr int kTabOddFull = 19;
-// Gradient accumulators: rows 2s (d/d alpha) and 2s+1 (d/d beta), s = 0..8
-// (grid g -> s = g, moment 0 -> s = 8).
-constexpr int kGradRows = 18;
+// Gradient accumulators: row s = dL/dc of coefficient set s (grid s in storage
+// order, 8 = moment 0); with anisotropic scattering rows 2s and 2s + 1 =
+// dL/d(mean sigma_a) and dL/d(mean sigma_s) of grid s.
+__host__ __device__ constexpr int grad_rows(bool aniso) { return aniso ? 16 : 9; }
 
 struct GridDesc {
     int nx, ny, nz;
@@ -62,10 +63,12 @@ int win_depth(int prec, int nx, int N, bool aniso);
 int adj_depth(int prec);
 
 // Anisotropic scattering: gl = device array of g_0 .. g_N (g_0 = 1), or
-// nullptr for the isotropic tables; tau = length of the substep.
+// nullptr for the isotropic tables; tau = length of the substep; opening:
+// (transposed sweeps) an odd half step whose later neighbour is a full one.
 struct Aniso {
     const double* gl;
     double tau;
+    int opening;
 };
 
 // aniso: rows 2s, 2s + 1 hold the means of sigma_a and sigma_s on grid s
@@ -76,12 +79,11 @@ hipError_t launch_tables(const double* sa, const double* ss, const double* q, do
 // the other rows rounded (kTabRows rows of n values)
 hipError_t launch_tables_f32(const double* tab, float* tabf, long long n, hipStream_t st);
 
-// Planes of a sweep, as element offsets from one base pointer (the pool):
-// src = first plane of the dual parity (the sources), tin / tout = first
-// target plane read / written (equal for an update in place); for the
-// target side of the transpose also aux = first target plane of the old
-// state and w = first plane of the output beta * lam.  Slot numbers in the
-// streams count from the first plane of their parity.
+// Planes of a sweep, as element offsets from one base pointer: src = first
+// plane of the dual parity (the sources), tin / tout = first target plane
+// read / written (equal for an update in place); for the transposed sweep
+// also aux / w = first target plane of the state before / after the substep.
+// Slot numbers in the streams count from the first plane of their parity.
 struct StateOffs {
     long long src, tin, tout, aux, w;
 };
@@ -121,21 +123,27 @@ struct TileArgs {
     const void* coef;
 };
 bool tile_use(int prec, int N, const GridDesc& g, TileGeom& tg);  // and fills tg
-int tile_depth(int prec, int nd);
+int tile_depth(int prec, int nd, bool adj);
 hipError_t launch_sweep_tile(int prec, void* pool, StateOffs so, const double* tab, const float* tabf,
                              int rowbase, const TileArgs& a, const TileGeom& tg, const GridDesc& g,
                              hipStream_t st);
+// Transposed substep, as launch_adj_win (isotropic).
+hipError_t launch_adj_tile(int prec, void* pool, StateOffs so, double* gp, const double* tab, int rowbase,
+                           double tau, int opening, const TileArgs& a, const TileGeom& tg, const GridDesc& g,
+                           hipStream_t st);
 
-// Transposed substep on the window streams.  side 0 (target side): so.src /
-// so.aux = dual / target half of the old state, tin = tout = cotangent lam
-// of the targets (updated), w = output beta * lam, gp = per-pass gradient
-// rows of this parity ([npass][kGradRows][ncell], added to).  side 1 (dual
-// side): src = the w half, tin = tout = lam of the dual moments.  FP64 and
-// FP32 only.  With anisotropic scattering the gradient rows 2s and 2s + 1
-// are dL/d(mean sigma_a) and dL/d(mean sigma_s) of grid s.
-hipError_t launch_adj_win(int prec, int side, void* pool, StateOffs so, double* gp,
-                          const double* tab, int rowbase, Aniso an, WinArgs a, GridDesc g,
-                          hipStream_t st);
+// Transposed substep on the window streams: src / tin = tout = the dual and
+// target halves of w (beta times the cotangent, see kernels.hip), aux / w =
+// target half of the state before / after the substep, gp = per-pass
+// gradient rows of this parity ([npass][grad_rows][ncell], added to).  FP64
+// and FP32 only.
+hipError_t launch_adj_win(int prec, void* pool, StateOffs so, double* gp, const double* tab, int rowbase,
+                          Aniso an, WinArgs a, GridDesc g, hipStream_t st);
+// Start of the reverse pass: w of moment 0 from its cotangent lam, and the
+// last even substep's gradient from moment 0 before and after it.
+hipError_t launch_adj_seed(int prec, const double* lam, void* w, const void* pre, const void* post,
+                           const double* tab, bool aniso, double tau, double* gp, long long n, hipStream_t st);
+// grad[i] = sum over nbuf buffers of n values
 hipError_t launch_grad_sum(const double* gp, int nbuf, double* grad, long long n, hipStream_t st);
 
 hipError_t launch_to_f64(int prec, const void* src_plane, double* dst, long long n,
@@ -151,9 +159,8 @@ hipError_t launch_check(int prec, const void* u, int nplanes, GridDesc g, double
                         unsigned long long* pcount, int npart, double* out_max,
                         unsigned long long* out_count, hipStream_t st);
 
-hipError_t launch_grad_final(const double* grad, const double* tab, const double* sa,
-                             const double* ss, double* dsa, double* dss, GridDesc g, double dt,
-                             bool aniso, hipStream_t st);
+hipError_t launch_grad_final(const double* grad, double* dsa, double* dss, GridDesc g, bool aniso,
+                             hipStream_t st);
 
 hipError_t launch_fill_zero(void* p, long long bytes, hipStream_t st);
 

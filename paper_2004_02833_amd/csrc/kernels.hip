@@ -13,6 +13,7 @@
 #include <cstdint>
 #include <type_traits>
 
+#include "decay.h"
 #include "kernels.h"
 
 // Target degrees per pass: registers (hence resident waves) and balanced
@@ -165,20 +166,6 @@ __constant__ int c_grid_bits[8] = {0, 3, 5, 6, 1, 2, 4, 7};
 __device__ __forceinline__ void decay(double c, double tau, double& a, double& b) {
     a = exp(-c * tau);
     b = (c == 0.0) ? tau : -expm1(-c * tau) / c;
-}
-
-// d beta / d c for beta = (1 - exp(-c tau))/c:  -tau^2 F(c tau) with
-// F(z) = (1 - (1+z) e^{-z}) / z^2 = sum_k (-1)^k (k+1) z^k / (k+2)!,
-// summed as a series for |z| < 1e-2 (truncation below 1e-16 relative).
-__device__ __forceinline__ double dbeta_series(double z, double tau) {
-    const double F = 0.5 + z * (-1.0 / 3.0 + z * (1.0 / 8.0 + z * (-1.0 / 30.0 + z * (1.0 / 144.0 - z / 840.0))));
-    return -tau * tau * F;
-}
-
-__device__ __forceinline__ double dbeta_dc(double c, double tau, double alpha, double beta) {
-    const double z = c * tau;
-    if (fabs(z) < 1e-2) return dbeta_series(z, tau);
-    return (tau * alpha - beta) / c;
 }
 
 // Cell k + b (b in {0,1}^3, sign +1) or k - b (sign -1), periodic.
@@ -573,18 +560,24 @@ __device__ __forceinline__ long long tile_cell(const TileMap& m, long long tile,
     return (long long)x + (long long)g.nx * ((long long)y + (long long)g.ny * z);
 }
 
-// Finalisation modes of the window sweep:
-//   kFwd     substep of eq. (5): u_i <- alpha u_i + beta (q_i - S_i)
-//   kAdjTgt  transpose, target side: with lam_i the cotangent of the updated
-//            u_i and S_i recomputed from the old state (its dual half at
-//            so.src, its target half at so.aux), add
-//            lam_i u_i and lam_i (q_i - S_i) to the gradients of alpha and
-//            beta of the target's coefficient set, write w_i = beta lam_i
-//            and lam_i <- alpha lam_i
-//   kAdjDual transpose, dual side: lam_j <- lam_j + S_j with the sources
-//            read from w (the transpose of a forward difference is minus the
-//            backward one, so this is a forward-shaped stencil over w)
-enum SweepMode { kFwd = 0, kAdjTgt = 1, kAdjDual = 2 };
+// Modes of the window sweep:
+//   kFwd  substep of eq. (5): u_i <- alpha u_i + beta (q_i - S_i)
+//   kAdj  one transposed substep.  With lam the cotangent of the state after
+//         a substep with targets i and dual moments j, its transpose is
+//             w_i = beta lam_i,  lam_j += S_j(w),  lam_i <- alpha lam_i
+//         (the transpose of a forward difference is minus the backward one,
+//         so S_j is the forward-shaped stencil over w).  Held as w instead of
+//         lam, the transpose runs as a forward sweep: the targets' w were
+//         left by their previous (later) substep of the same length, so
+//             w_i <- alpha w_i + beta S_i(w_j)
+//         with the dual side's w as the sources; for the opening half step,
+//         whose later neighbour is a full step, alpha becomes
+//         alpha_full beta_half / beta_full = alpha^2 / (1 + alpha).
+//         The gradient of the substep needs lam_i u_i and lam_i r_i with
+//         r_i = (u_i' - alpha u_i) / beta from the target's values before
+//         (so.aux) and after (so.w) the substep: no second stencil, and per
+//         coefficient set two sums of products with w, combined at the end.
+enum SweepMode { kFwd = 0, kAdj = 1 };
 
 // Resident waves per SIMD asked of the compiler for the whole-row forward
 // sweeps (register budget 512 / waves, checked free of spills); 1 leaves the
@@ -601,12 +594,9 @@ enum SweepMode { kFwd = 0, kAdjTgt = 1, kAdjDual = 2 };
 template <class T> struct MinWaves { static constexpr int v = PM_WPE16; };
 template <> struct MinWaves<double> { static constexpr int v = PM_WPE64; };
 template <> struct MinWaves<float> { static constexpr int v = PM_WPE32; };
-// and for the FP64 transposed sweeps (target side, dual side)
+// and for the FP64 transposed sweeps
 #ifndef PM_WPE64_ADJ
-#define PM_WPE64_ADJ 4
-#endif
-#ifndef PM_WPE64_DUAL
-#define PM_WPE64_DUAL 4
+#define PM_WPE64_ADJ 1   // 136-156 VGPRs, 3 waves; held to 4 it spills
 #endif
 // Unused rows added to the LDS table array (a cap on resident workgroups
 // for tuning; 0 in use).
@@ -669,10 +659,10 @@ constexpr int min_waves() {
     if (MODE == kFwd && XM == kXLoad && !ANI && std::is_same<T, float>::value && CPL == 1) return PM_WPE32N;
     if (MODE == kFwd) return XM == kXRow && !ANI ? MinWaves<T>::v : 1;
     if (!std::is_same<T, double>::value || ANI) return 1;
-    return MODE == kAdjTgt ? PM_WPE64_ADJ : PM_WPE64_DUAL;
+    return PM_WPE64_ADJ;
 }
 
-// One kernel for the forward substep and both halves of its transpose.
+// One kernel for the forward substep and its transpose.
 // ANI (anisotropic scattering): the table rows of the four target grids hold
 // the means of sigma_a and sigma_s; the decay factors of every (target
 // degree, grid) pair of the pass are formed once per cell from
@@ -686,10 +676,9 @@ k_sweep_win(T* __restrict__ pool, StateOffs so, double* __restrict__ gp,
             const double* __restrict__ tab, const float* __restrict__ tabf,
             const int2* __restrict__ src, const int2* __restrict__ tgt,
             const typename Acc<T>::type* __restrict__ coef, const double* __restrict__ gl,
-            double tau, int rowbase, int N, int parity, int npass, int per_xcd, long long ntile,
+            double tau, int opening, int rowbase, int N, int parity, int npass, int per_xcd, long long ntile,
             TileMap tm, GridDesc g) {
     static_assert(MODE == kFwd || CPL == 1, "transposed sweeps use one cell per lane");
-    static_assert(!(ANI && MODE == kAdjDual), "the dual side reads no decay factors");
     // every plane is addressed from one base: sources (the dual parity),
     // targets read and written (equal offsets for an update in place)
     const T* sv = pool + so.src;
@@ -763,7 +752,7 @@ k_sweep_win(T* __restrict__ pool, StateOffs so, double* __restrict__ gp,
                     tl[2 * (4 * t + f) + 1][tid * CPL + k] = b;
                 }
             }
-    } else if (MODE != kAdjDual) {
+    } else {
 #pragma unroll
         for (int f = 0; f < 8; ++f)
 #pragma unroll
@@ -771,11 +760,12 @@ k_sweep_win(T* __restrict__ pool, StateOffs so, double* __restrict__ gp,
                 tl[f][tid * CPL + k] = kF32Update ? (TabT)tabf[(long long)(rowbase + f) * g.ncell + nb.c0 + k]
                                                   : (TabT)tab[(long long)(rowbase + f) * g.ncell + nb.c0 + k];
     }
-    // kAdjTgt gradient sums: per coefficient set (isotropic), or per grid
-    // with respect to the means of sigma_a (ga) and sigma_s (gb) (ANI)
-    double ga[5] = {0, 0, 0, 0, 0}, gb[5] = {0, 0, 0, 0, 0};
+    // kAdj gradient sums: sum w u and sum w u' per coefficient set
+    // (isotropic), or dL/d(mean sigma_a) and dL/d(mean sigma_s) per grid (ANI)
+    double ga[4] = {0, 0, 0, 0}, gb[4] = {0, 0, 0, 0};
+    double* gq = MODE == kAdj ? gp + (long long)pass * grad_rows(ANI) * g.ncell + nb.c0 : nullptr;
     // moment 0 (and its source q) is a target of the first even pass only
-    if (MODE != kAdjDual && parity == 0 && pass == 0) {
+    if (parity == 0 && pass == 0) {
 #pragma unroll
         for (int k = 0; k < CPL; ++k) {
             if (!ANI) {
@@ -784,7 +774,7 @@ k_sweep_win(T* __restrict__ pool, StateOffs so, double* __restrict__ gp,
                 tl[9][tid * CPL + k] = kF32Update ? (TabT)tabf[(long long)(kTabMom0 + 1) * g.ncell + nb.c0 + k]
                                                   : (TabT)tab[(long long)(kTabMom0 + 1) * g.ncell + nb.c0 + k];
             }
-            tl[kRowQ][tid * CPL + k] = (kF32Update && !ANI) ? (TabT)tabf[(long long)kTabQ * g.ncell + nb.c0 + k]
+            if (MODE == kFwd) tl[kRowQ][tid * CPL + k] = (kF32Update && !ANI) ? (TabT)tabf[(long long)kTabQ * g.ncell + nb.c0 + k]
                                                             : (TabT)tab[(long long)kTabQ * g.ncell + nb.c0 + k];
         }
     }
@@ -795,17 +785,21 @@ k_sweep_win(T* __restrict__ pool, StateOffs so, double* __restrict__ gp,
 
     Raw<T, CPL> R[K + 1][2];  // raw values of the current source column
     // forward sweep: old values of the targets finished in the next column,
-    // requested one column ahead (transposed modes read theirs in place)
+    // requested one column ahead (the transpose requests its three values
+    // per target together when it finishes a column: held a column ahead
+    // they cost FP64 a wave per SIMD)
     typename Pack<T, CPL>::V tpf[K][2];
-    if constexpr (MODE == kFwd) {
+    auto request = [&](const int2* tdn) {
 #pragma unroll
         for (int t = 0; t < K; ++t)
 #pragma unroll
             for (int ty = 0; ty < 2; ++ty) {
-                const int2 dn = td[t * 2 + ty];
-                tpf[t][ty] = dn.x >= 0 ? __builtin_nontemporal_load((const V*)(tin + (long long)dn.x * ps + nb.c0)) : V{};
+                const int2 dn = tdn[t * 2 + ty];
+                const long long at = (long long)dn.x * ps + nb.c0;
+                tpf[t][ty] = dn.x >= 0 ? __builtin_nontemporal_load((const V*)(tin + at)) : V{};
             }
-    }
+    };
+    if constexpr (MODE == kFwd) request(td);
     A S[3][K][2][CPL];        // partial sums: target columns mu-1, mu, mu+1
 #pragma unroll
     for (int b = 0; b <= K; ++b)
@@ -896,24 +890,22 @@ k_sweep_win(T* __restrict__ pool, StateOffs so, double* __restrict__ gp,
         if (mu >= 1) {
             const int2* tdc = td + (mu - 1) * K * 2;
             typename Pack<T, CPL>::V tcur[K][2];
-            if constexpr (MODE == kFwd) {
+            T upre[K][2], upost[K][2];
 #pragma unroll
-                for (int t = 0; t < K; ++t)
+            for (int t = 0; t < K; ++t)
 #pragma unroll
-                    for (int ty = 0; ty < 2; ++ty) tcur[t][ty] = tpf[t][ty];
-                {
-                    const int2* tdn = td + mu * K * 2;
-#pragma unroll
-                    for (int t = 0; t < K; ++t)
-#pragma unroll
-                        for (int ty = 0; ty < 2; ++ty) {
-                            const int2 dn = tdn[t * 2 + ty];
-                            tpf[t][ty] = dn.x >= 0 ? __builtin_nontemporal_load(
-                                                         (const V*)(tin + (long long)dn.x * ps + nb.c0))
-                                                   : V{};
-                        }
+                for (int ty = 0; ty < 2; ++ty) {
+                    if constexpr (MODE == kFwd) {
+                        tcur[t][ty] = tpf[t][ty];
+                    } else {
+                        const int2 d = tdc[t * 2 + ty];
+                        const long long at = (long long)d.x * ps + nb.c0;
+                        tcur[t][ty] = d.x >= 0 ? __builtin_nontemporal_load((const V*)(tin + at)) : V{};
+                        upre[t][ty] = d.x >= 0 ? __builtin_nontemporal_load(pool + so.aux + at) : T{};
+                        upost[t][ty] = d.x >= 0 ? __builtin_nontemporal_load(pool + so.w + at) : T{};
+                    }
                 }
-            }
+            if constexpr (MODE == kFwd) request(td + mu * K * 2);
 #pragma unroll
             for (int t = 0; t < K; ++t) {
 #pragma unroll
@@ -928,10 +920,7 @@ k_sweep_win(T* __restrict__ pool, StateOffs so, double* __restrict__ gp,
                                        : m0 ? 8 : 2 * ((d.y >> 1) & 3);
                     T* ut = tout + (long long)d.x * ps + nb.c0;
                     A old[CPL];
-                    if constexpr (MODE == kFwd)
-                        unpack<T, CPL, A>(tcur[t][ty], old);
-                    else
-                        unpack<T, CPL, A>(__builtin_nontemporal_load((const V*)(tin + (long long)d.x * ps + nb.c0)), old);
+                    unpack<T, CPL, A>(tcur[t][ty], old);
                     if constexpr (MODE == kFwd && kF32Update) {
                         float nf[CPL];
 #pragma unroll
@@ -953,27 +942,15 @@ k_sweep_win(T* __restrict__ pool, StateOffs so, double* __restrict__ gp,
                             nv[k] = tl[ra][tid * CPL + k] * (double)old[k] +
                                     tl[ra + 1][tid * CPL + k] * (q - (double)S[0][t][ty][k]);
                         }
-                    } else if constexpr (MODE == kAdjDual) {
-                        nv[0] = (double)old[0] + (double)S[0][t][ty][0];
                     } else {
-                        // old[0] is lam_i; the old u_i comes from the source state
-                        const double lam = (double)old[0];
-                        const double uo = (double)ld(pool + so.aux + (long long)d.x * ps + nb.c0);
-                        const double q = m0 ? tl[kRowQ][tid] : 0.0;
-                        const double r = q - (double)S[0][t][ty][0];
+                        const double al = tl[ra][tid], be = tl[ra + 1][tid];
+                        const double a = opening ? al * al / (1.0 + al) : al;
+                        nv[0] = a * (double)old[0] + be * (double)S[0][t][ty][0];
+                        const double u0 = (double)upre[t][ty], u1 = (double)upost[t][ty];
+                        const int f = (d.y >> 1) & 3;
                         if constexpr (ANI) {
-                            // dL/dc = lam (u d alpha/dc + r d beta/dc), with c
-                            // recovered from the factors: c = (1 - alpha)/beta
-                            const double al = tl[ra][tid], be = tl[ra + 1][tid];
-                            const double om = 1.0 - al;
-                            double db;
-                            if (om < 1e-2)
-                                db = dbeta_series(tau * om / be, tau);
-                            else
-                                db = (tau * al - be) * be / om;
-                            const double gx = lam * (uo * (-tau * al) + r * db);
+                            const double gx = dl_dc(nv[0] * u0, nv[0] * u1, al, be, tau);
                             const double ws = 1.0 - gl[L0 + 2 * t];
-                            const int f = (d.y >> 1) & 3;
 #pragma unroll
                             for (int f4 = 0; f4 < 4; ++f4)
                                 if (f4 == f) {
@@ -981,17 +958,17 @@ k_sweep_win(T* __restrict__ pool, StateOffs so, double* __restrict__ gp,
                                     gb[f4] += ws * gx;
                                 }
                         } else {
-                            const int set = m0 ? 4 : ((d.y >> 1) & 3);
+                            if (m0) {  // the one target of its set
+                                if (live) gq[8 * g.ncell] += dl_dc(nv[0] * u0, nv[0] * u1, al, be, tau);
+                            } else {
 #pragma unroll
-                            for (int s5 = 0; s5 < 5; ++s5)
-                                if (s5 == set) {
-                                    ga[s5] += lam * uo;
-                                    gb[s5] += lam * r;
-                                }
+                                for (int f4 = 0; f4 < 4; ++f4)
+                                    if (f4 == f) {
+                                        ga[f4] += nv[0] * u0;
+                                        gb[f4] += nv[0] * u1;
+                                    }
+                            }
                         }
-                        const double wv[1] = {tl[ra + 1][tid] * lam};
-                        if (live) st(pool + so.w + (long long)d.x * ps + nb.c0, wv[0]);
-                        nv[0] = tl[ra][tid] * lam;
                     }
                     if (live) __builtin_nontemporal_store(pack<T, CPL>(nv), (V*)ut);
                 }
@@ -1014,22 +991,59 @@ k_sweep_win(T* __restrict__ pool, StateOffs so, double* __restrict__ gp,
         // wave of a workgroup runs the same pass, so all reach it equally often.
         if constexpr (XM == kXRow) __syncthreads();
     }
-    if constexpr (MODE == kAdjTgt) {
-        // gradient rows of this pass (2 s for alpha, 2 s + 1 for beta, s the
-        // coefficient set: grid order, 8 for moment 0); one workgroup owns
-        // every (pass, cell), so the accumulation needs no atomics
+    if constexpr (MODE == kAdj) {
+        // gradient rows of this pass: dL/dc of set s in row s (grid order, 8
+        // for moment 0), ANI: dL/d(mean sigma_a) and dL/d(mean sigma_s) of
+        // grid s in rows 2 s and 2 s + 1; one workgroup owns every
+        // (pass, cell), so the accumulation needs no atomics
         if (live) {
-            double* gq = gp + (long long)pass * kGradRows * g.ncell + nb.c0;
             const int gbase = parity ? 4 : 0;
 #pragma unroll
-            for (int s5 = 0; s5 < 5; ++s5) {
-                if (s5 == 4 && (parity != 0 || ANI)) continue;
-                const int row = s5 == 4 ? kTabMom0 : 2 * (gbase + s5);
-                gq[(long long)row * g.ncell] += ga[s5];
-                gq[(long long)(row + 1) * g.ncell] += gb[s5];
+            for (int f = 0; f < 4; ++f) {
+                if constexpr (ANI) {
+                    gq[(long long)(2 * (gbase + f)) * g.ncell] += ga[f];
+                    gq[(long long)(2 * (gbase + f) + 1) * g.ncell] += gb[f];
+                } else {
+                    gq[(long long)(gbase + f) * g.ncell] += dl_dc(ga[f], gb[f], tl[2 * f][tid], tl[2 * f + 1][tid], tau);
+                }
             }
         }
     }
+}
+
+// Cotangent of moment 0 at the end of a recorded run: w = beta lam there
+// (tau = dt) and zero elsewhere, and the last even substep's share of the
+// gradient (pre, post: moment 0 before and after it).
+template <class T>
+__global__ void k_adj_seed(const double* __restrict__ lam, T* __restrict__ w, const T* __restrict__ pre,
+                           const T* __restrict__ post, const double* __restrict__ tab, int aniso, double tau,
+                           double* __restrict__ gp, long long n) {
+    const long long c = (long long)blockIdx.x * blockDim.x + threadIdx.x;
+    if (c >= n) return;
+    double al, be;
+    if (aniso) {
+        decay(tab[c], tau, al, be);
+    } else {
+        al = tab[(long long)kTabMom0 * n + c];
+        be = tab[(long long)(kTabMom0 + 1) * n + c];
+    }
+    const double v = be * lam[c];
+    st(w + c, v);
+    gp[(aniso ? 0 : 8) * n + c] += dl_dc(v * (double)ld(pre + c), v * (double)ld(post + c), al, be, tau);
+}
+
+hipError_t launch_adj_seed(int prec, const double* lam, void* w, const void* pre, const void* post, const double* tab,
+                           bool aniso, double tau, double* gp, long long n, hipStream_t st) {
+    const dim3 nb((unsigned)((n + 255) / 256)), b(256);
+    if (prec == kF64)
+        hipLaunchKernelGGL(k_adj_seed<double>, nb, b, 0, st, lam, (double*)w, (const double*)pre, (const double*)post, tab,
+                           aniso ? 1 : 0, tau, gp, n);
+    else if (prec == kF32)
+        hipLaunchKernelGGL(k_adj_seed<float>, nb, b, 0, st, lam, (float*)w, (const float*)pre, (const float*)post, tab,
+                           aniso ? 1 : 0, tau, gp, n);
+    else
+        return hipErrorInvalidValue;
+    return hipGetLastError();
 }
 
 // Deepest forward pass instantiated for FP64 and FP32 (3, or 4 for tuning).
@@ -1103,7 +1117,7 @@ static void launch_win_t(T* pool, StateOffs so, double* gp, const double* tab, c
     if (sw == g.nx && g.nx == 64 * CPL) {
         hipLaunchKernelGGL((k_sweep_win<T, K, TPB, CPL, MODE, ANI, kXRow>), dim3(nwg),
                            dim3(TPB), 0, st, pool, so, gp, tab, tabf, a.src, a.tgt, (const A*)a.coef,
-                           an.gl, an.tau, rowbase, a.N, a.parity, a.npass, per_xcd, ntile, tm, g);
+                           an.gl, an.tau, an.opening, rowbase, a.N, a.parity, a.npass, per_xcd, ntile, tm, g);
         return;
     }
     {
@@ -1123,14 +1137,14 @@ static void launch_win_t(T* pool, StateOffs so, double* gp, const double* tab, c
             const unsigned nw = (unsigned)((long long)kXcds * px * a.npass);
             hipLaunchKernelGGL((k_sweep_win<T, K, TPB, CPL, MODE, ANI, kXLoad>), dim3(nw),
                                dim3(TPB), 0, st, pool, so, gp, tab, tabf, a.src, a.tgt,
-                               (const A*)a.coef, an.gl, an.tau, rowbase, a.N, a.parity, a.npass,
+                               (const A*)a.coef, an.gl, an.tau, an.opening, rowbase, a.N, a.parity, a.npass,
                                px, nt, tc, g);
             return;
         }
     }
     hipLaunchKernelGGL((k_sweep_win<T, K, TPB, CPL, MODE, ANI, kXLoad>), dim3(nwg), dim3(TPB),
                        0, st, pool, so, gp, tab, tabf, a.src, a.tgt, (const A*)a.coef, an.gl,
-                       an.tau, rowbase, a.N, a.parity, a.npass, per_xcd, ntile, tm, g);
+                       an.tau, an.opening, rowbase, a.N, a.parity, a.npass, per_xcd, ntile, tm, g);
 }
 
 template <class T, int K, int CPL>
@@ -1178,24 +1192,21 @@ hipError_t launch_sweep_win(int prec, void* pool, StateOffs so, const double* ta
 }
 
 template <class T, int K>
-static void launch_adj_t(int side, void* pool, StateOffs so, double* gp, const double* tab,
-                         int rowbase, Aniso an, WinArgs a, GridDesc g, hipStream_t st) {
-    if (side == 1)
-        launch_win_t<T, K, 1, kAdjDual, false>((T*)pool, so, nullptr, tab, nullptr, 0, an, a, g, st);
-    else if (an.gl)
-        launch_win_t<T, K, 1, kAdjTgt, true>((T*)pool, so, gp, tab, nullptr, rowbase, an, a, g, st);
+static void launch_adj_t(void* pool, StateOffs so, double* gp, const double* tab, int rowbase, Aniso an, WinArgs a,
+                         GridDesc g, hipStream_t st) {
+    if (an.gl)
+        launch_win_t<T, K, 1, kAdj, true>((T*)pool, so, gp, tab, nullptr, rowbase, an, a, g, st);
     else
-        launch_win_t<T, K, 1, kAdjTgt, false>((T*)pool, so, gp, tab, nullptr, rowbase, an, a, g, st);
+        launch_win_t<T, K, 1, kAdj, false>((T*)pool, so, gp, tab, nullptr, rowbase, an, a, g, st);
 }
 
-hipError_t launch_adj_win(int prec, int side, void* pool, StateOffs so, double* gp,
-                          const double* tab, int rowbase, Aniso an, WinArgs a, GridDesc g,
-                          hipStream_t st) {
+hipError_t launch_adj_win(int prec, void* pool, StateOffs so, double* gp, const double* tab, int rowbase, Aniso an,
+                          WinArgs a, GridDesc g, hipStream_t st) {
     if (a.K != adj_depth(prec) || prec == kBF16) return hipErrorInvalidValue;
     if (prec == kF64)
-        launch_adj_t<double, PM_ADJ_K64>(side, pool, so, gp, tab, rowbase, an, a, g, st);
+        launch_adj_t<double, PM_ADJ_K64>(pool, so, gp, tab, rowbase, an, a, g, st);
     else
-        launch_adj_t<float, PM_ADJ_K32>(side, pool, so, gp, tab, rowbase, an, a, g, st);
+        launch_adj_t<float, PM_ADJ_K32>(pool, so, gp, tab, rowbase, an, a, g, st);
     return hipGetLastError();
 }
 
@@ -1203,16 +1214,14 @@ hipError_t launch_adj_win(int prec, int side, void* pool, StateOffs so, double* 
 __global__ void k_grad_sum(const double* __restrict__ gp, int nbuf, double* __restrict__ grad,
                            long long n) {
     const long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= (long long)kGradRows * n) return;
+    if (i >= n) return;
     double acc = 0.0;
-    for (int b = 0; b < nbuf; ++b) acc += gp[(long long)b * kGradRows * n + i];
+    for (int b = 0; b < nbuf; ++b) acc += gp[(long long)b * n + i];
     grad[i] = acc;
 }
 
 hipError_t launch_grad_sum(const double* gp, int nbuf, double* grad, long long n, hipStream_t st) {
-    const long long tot = (long long)kGradRows * n;
-    hipLaunchKernelGGL(k_grad_sum, dim3((unsigned)((tot + 255) / 256)), dim3(256), 0, st, gp, nbuf,
-                       grad, n);
+    hipLaunchKernelGGL(k_grad_sum, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, gp, nbuf, grad, n);
     return hipGetLastError();
 }
 
@@ -1410,38 +1419,27 @@ hipError_t launch_check(int prec, const void* u, int nplanes, GridDesc g, double
 }
 
 // ----------------------------------------------------------------- adjoint --
-// The transposed substeps run on the window sweep (modes kAdjTgt/kAdjDual
-// above); what remains is the chain rule from the decay factors to the
-// cell-centred medium.
-
+// The transposed substeps run on the window sweep (mode kAdj above), which
+// leaves dL/dc per coefficient set; what remains is the chain rule from the
+// staggered coefficients to the cell-centred medium.
 
 // Chain rule to the cell-centred medium: per set s the coefficient c_s on
 // the set's points is the mean of (sigma_a [+ sigma_s]) over 2^k cells
-// c + b; its transpose gathers g_s from the cells c - b.
-__global__ void k_grad_final(const double* __restrict__ grad, const double* __restrict__ tab,
-                             const double* __restrict__ sa, const double* __restrict__ ss,
-                             double* __restrict__ dsa, double* __restrict__ dss, GridDesc g,
-                             double dt) {
+// c + b; its transpose gathers dL/dc_s from the cells c - b.
+__global__ void k_grad_final(const double* __restrict__ grad, double* __restrict__ dsa, double* __restrict__ dss,
+                             GridDesc g) {
     const long long c = (long long)blockIdx.x * blockDim.x + threadIdx.x;
     if (c >= g.ncell) return;
     double ta = 0.0, ts = 0.0;
     for (int s = 0; s < 9; ++s) {
         const int bits = s < 8 ? c_grid_bits[s] : 0;
         const int ox = bits & 1, oy = (bits >> 1) & 1, oz = (bits >> 2) & 1;
-        const double tau = set_tau(s, dt);
-        const int row = s < 8 ? 2 * s : kTabMom0;
         double acc = 0.0;
         int cnt = 0;
         for (int bz = 0; bz <= oz; ++bz)
             for (int by = 0; by <= oy; ++by)
                 for (int bx = 0; bx <= ox; ++bx) {
-                    const long long k = shifted(c, bx, by, bz, true, g);
-                    const double a = tab[(long long)row * g.ncell + k];
-                    const double b = tab[(long long)(row + 1) * g.ncell + k];
-                    const double cc = cbar_at(sa, ss, k, s, g);
-                    const double ga = grad[(long long)(2 * s) * g.ncell + k];
-                    const double gb = grad[(long long)(2 * s + 1) * g.ncell + k];
-                    acc += ga * (-tau * a) + gb * dbeta_dc(cc, tau, a, b);
+                    acc += grad[(long long)s * g.ncell + shifted(c, bx, by, bz, true, g)];
                     ++cnt;
                 }
         acc /= cnt;
@@ -1480,15 +1478,12 @@ __global__ void k_grad_final_aniso(const double* __restrict__ grad, double* __re
     if (dss) dss[c] = ts;
 }
 
-hipError_t launch_grad_final(const double* grad, const double* tab, const double* sa,
-                             const double* ss, double* dsa, double* dss, GridDesc g, double dt,
-                             bool aniso, hipStream_t st) {
+hipError_t launch_grad_final(const double* grad, double* dsa, double* dss, GridDesc g, bool aniso, hipStream_t st) {
     const unsigned nb = (unsigned)((g.ncell + 255) / 256);
     if (aniso)
         hipLaunchKernelGGL(k_grad_final_aniso, dim3(nb), dim3(256), 0, st, grad, dsa, dss, g);
     else
-        hipLaunchKernelGGL(k_grad_final, dim3(nb), dim3(256), 0, st, grad, tab, sa, ss, dsa, dss,
-                           g, dt);
+        hipLaunchKernelGGL(k_grad_final, dim3(nb), dim3(256), 0, st, grad, dsa, dss, g);
     return hipGetLastError();
 }
 

@@ -18,6 +18,7 @@
 #include <cstdint>
 #include <type_traits>
 
+#include "decay.h"
 #include "kernels.h"
 
 namespace pm {
@@ -40,12 +41,14 @@ __device__ __forceinline__ void wait_copies() {
 
 constexpr int kXcd = 8;
 
-template <class T, int K, int TPB, int QMAX, bool NT>
+template <class T, int K, int TPB, int QMAX, bool NT, bool ADJ>
 __global__ void __launch_bounds__(TPB, 4)
-k_sweep_tile(T* __restrict__ pool, StateOffs so, const T* __restrict__ tab,
+k_sweep_tile(T* __restrict__ pool, StateOffs so, double* __restrict__ gp,
+             const typename std::conditional<ADJ, double, T>::type* __restrict__ tab,
              const uint32_t* __restrict__ src, const uint32_t* __restrict__ tgt,
-             const T* __restrict__ coef, int rowbase, int N, int parity, int npass,
-             int per_xcd, TileGeom tg, GridDesc g) {
+             const T* __restrict__ coef, double tau, int opening, int rowbase, int N, int parity,
+             int npass, int per_xcd, TileGeom tg, GridDesc g) {
+    using TabT = typename std::conditional<ADJ, double, T>::type;
     constexpr int E = 16 / (int)sizeof(T);
     constexpr int IMG = QMAX * 16;
     constexpr int BUF = (K + 1) * IMG;
@@ -172,22 +175,40 @@ k_sweep_tile(T* __restrict__ pool, StateOffs so, const T* __restrict__ tab,
 
     const int mumax = min(N, L0 + 2 * (K - 1));
     // decay factors of the four target grids: [type][(mu + parity) mod 2]
-    T fa[2][2], fb[2][2];
+    TabT fa[2][2], fb[2][2];
+    auto trow = [&](int row) {
+        return *(const TabT*)((const char*)(tab + (long long)row * g.ncell) + (uint32_t)c * (uint32_t)sizeof(TabT));
+    };
 #pragma unroll
     for (int ty = 0; ty < 2; ++ty)
 #pragma unroll
         for (int m = 0; m < 2; ++m) {
-            fa[ty][m] = tab[(long long)(rowbase + 2 * (ty + 2 * m)) * g.ncell + c];
-            fb[ty][m] = tab[(long long)(rowbase + 2 * (ty + 2 * m) + 1) * g.ncell + c];
+            fa[ty][m] = trow(rowbase + 2 * (ty + 2 * m));
+            fb[ty][m] = trow(rowbase + 2 * (ty + 2 * m) + 1);
+            if (ADJ && opening) fa[ty][m] = fa[ty][m] * fa[ty][m] / ((TabT)1 + fa[ty][m]);
         }
     T S[3][K][2];
     T old[K][2];
+    // transpose: the targets' values before and after the substep, and per
+    // target grid [type][(mu + parity) mod 2] the sums of w u and w u', each
+    // lane's own in LDS (in registers they spill)
+    T pre[ADJ ? K : 1][2], post[ADJ ? K : 1][2];
+    __shared__ double sums[ADJ ? 4 : 1][2][ADJ ? TPB : 1];
+    if constexpr (ADJ) {
+#pragma unroll
+        for (int f = 0; f < 4; ++f) sums[f][0][tid] = sums[f][1][tid] = 0.0;
+    }
+    // (32-bit byte offsets: a plane has less than 2^31 bytes)
+    auto grow = [&](int row) {
+        return (double*)((char*)(gp + ((long long)pass * grad_rows(false) + row) * g.ncell) + (uint32_t)c * 8u);
+    };
 #pragma unroll
     for (int t = 0; t < K; ++t)
 #pragma unroll
         for (int ty = 0; ty < 2; ++ty) {
             S[0][t][ty] = S[1][t][ty] = S[2][t][ty] = (T)0;
             old[t][ty] = (T)0;
+            if constexpr (ADJ) pre[t][ty] = post[t][ty] = (T)0;
         }
     // Whole cache lines are streamed past the caches (nt); where rows start
     // inside a line, neighbouring segments share it and must meet in L2.
@@ -205,6 +226,8 @@ k_sweep_tile(T* __restrict__ pool, StateOffs so, const T* __restrict__ tab,
     };
     const char* tin = (const char*)(pool + so.tin);
     char* tout = (char*)(pool + so.tout);
+    const char* upre = (const char*)(pool + so.aux);
+    const char* upost = (const char*)(pool + so.w);
     const uint32_t coff = (uint32_t)c * (uint32_t)sizeof(T);
 
     auto request = [&](int mu) {  // old values of target column mu
@@ -220,10 +243,20 @@ k_sweep_tile(T* __restrict__ pool, StateOffs so, const T* __restrict__ tab,
             if (t >= t0 && t < t1) {
                 old[t][0] = load((const T*)(tin + ((uint64_t)sl[t] << SH) + coff));
                 if (mu > 0) old[t][1] = load((const T*)(tin + ((uint64_t)sl[K + t] << SH) + coff));
+                if constexpr (ADJ) {
+                    pre[t][0] = load((const T*)(upre + ((uint64_t)sl[t] << SH) + coff));
+                    post[t][0] = load((const T*)(upost + ((uint64_t)sl[t] << SH) + coff));
+                    if (mu > 0) {
+                        pre[t][1] = load((const T*)(upre + ((uint64_t)sl[K + t] << SH) + coff));
+                        post[t][1] = load((const T*)(upost + ((uint64_t)sl[K + t] << SH) + coff));
+                    }
+                }
             }
     };
-    auto update = [&](T a, T b, T u, T r) {  // r = q - S
-        if constexpr (std::is_same<T, double>::value)
+    auto update = [&](TabT a, TabT b, T u, T r) {  // r = q - S, transpose: S
+        if constexpr (ADJ)
+            return a * (double)u + b * (double)r;
+        else if constexpr (std::is_same<T, double>::value)
             return a * u + b * r;
         else  // a = 1 - alpha
             return __builtin_fmaf(b, r, __builtin_fmaf(-a, u, u));
@@ -237,7 +270,7 @@ k_sweep_tile(T* __restrict__ pool, StateOffs so, const T* __restrict__ tab,
 #pragma unroll
         for (int t = 0; t < 2 * K; ++t) asm volatile("" ::"s"(sl[t]));
         const bool m1 = (mu & 1) != parity;
-        T al[2], be[2];
+        TabT al[2], be[2];
 #pragma unroll
         for (int ty = 0; ty < 2; ++ty) {
             al[ty] = m1 ? fa[ty][1] : fa[ty][0];
@@ -246,19 +279,32 @@ k_sweep_tile(T* __restrict__ pool, StateOffs so, const T* __restrict__ tab,
 #pragma unroll
         for (int t = 0; t < K; ++t)
             if (t >= t0 && t < t1) {
-                T a0 = al[0], b0 = be[0], q = (T)0;
-                if (t == 0 && L0 == 0 && mu == 0) {  // moment 0
-                    a0 = tab[(long long)kTabMom0 * g.ncell + c];
-                    b0 = tab[(long long)(kTabMom0 + 1) * g.ncell + c];
-                    q = tab[(long long)kTabQ * g.ncell + c];
+                TabT a0 = al[0], b0 = be[0], q = (TabT)0;
+                const bool mom0 = t == 0 && L0 == 0 && mu == 0;
+                if (mom0) {
+                    a0 = trow(kTabMom0);
+                    b0 = trow(kTabMom0 + 1);
+                    if constexpr (!ADJ) q = trow(kTabQ);
                     // arrived before the branch ends on every lane's path
                     asm volatile("" : "+v"(a0), "+v"(b0), "+v"(q));
                 }
-                const T v0 = update(a0, b0, old[t][0], q - S[0][t][0]);
-                const T v1 = update(al[1], be[1], old[t][1], -S[0][t][1]);
+                const TabT v0 = update(a0, b0, old[t][0], ADJ ? S[0][t][0] : (T)(q - S[0][t][0]));
+                const TabT v1 = update(al[1], be[1], old[t][1], ADJ ? S[0][t][1] : -S[0][t][1]);
+                if constexpr (ADJ) {
+                    if (mom0) {  // the one target of its set
+                        if (live) *grow(8) += dl_dc(v0 * (double)pre[t][0], v0 * (double)post[t][0], a0, b0, tau);
+                    } else {
+                        sums[m1 ? 1 : 0][0][tid] += v0 * (double)pre[t][0];
+                        sums[m1 ? 1 : 0][1][tid] += v0 * (double)post[t][0];
+                    }
+                    if (mu > 0) {
+                        sums[m1 ? 3 : 2][0][tid] += v1 * (double)pre[t][1];
+                        sums[m1 ? 3 : 2][1][tid] += v1 * (double)post[t][1];
+                    }
+                }
                 if (live) {
-                    store(v0, (T*)(tout + ((uint64_t)sl[t] << SH) + coff));
-                    if (mu > 0) store(v1, (T*)(tout + ((uint64_t)sl[K + t] << SH) + coff));
+                    store((T)v0, (T*)(tout + ((uint64_t)sl[t] << SH) + coff));
+                    if (mu > 0) store((T)v1, (T*)(tout + ((uint64_t)sl[K + t] << SH) + coff));
                 }
             }
     };
@@ -321,7 +367,10 @@ k_sweep_tile(T* __restrict__ pool, StateOffs so, const T* __restrict__ tab,
         // the old target values have arrived too: taken here, so that no
         // later wait for them also waits for the copies issued below
 #pragma unroll
-        for (int t = 0; t < K; ++t) asm volatile("" : "+v"(old[t][0]), "+v"(old[t][1]));
+        for (int t = 0; t < K; ++t) {
+            asm volatile("" : "+v"(old[t][0]), "+v"(old[t][1]));
+            if constexpr (ADJ) asm volatile("" : "+v"(pre[t][0]), "+v"(pre[t][1]), "+v"(post[t][0]), "+v"(post[t][1]));
+        }
         __syncthreads();
         issue(mu, 1);
         if (mu >= 2) finish(mu - 2);
@@ -343,14 +392,30 @@ k_sweep_tile(T* __restrict__ pool, StateOffs so, const T* __restrict__ tab,
         if (mu > 0) push(mu, std::integral_constant<int, 1>());
     }
     finish(mumax);
+    if constexpr (ADJ) {
+        // dL/dc of the parity's grids (row = grid in storage order); one
+        // workgroup owns every (pass, cell)
+        if (live) {
+#pragma unroll
+            for (int ty = 0; ty < 2; ++ty)
+#pragma unroll
+                for (int m = 0; m < 2; ++m) {
+                    const int f = ty + 2 * m;
+                    *grow((parity ? 4 : 0) + f) +=
+                        dl_dc(sums[2 * ty + m][0][tid], sums[2 * ty + m][1][tid], trow(rowbase + 2 * f), fb[ty][m], tau);
+                }
+        }
+    }
 }
 
-template <class T, int K, int TPB, int QMAX, bool NT>
-void launch_t(void* pool, StateOffs so, const void* tab, int rowbase, const TileArgs& a, const TileGeom& tg, const GridDesc& g, hipStream_t st) {
+template <class T, int K, int TPB, int QMAX, bool NT, bool ADJ>
+void launch_t(void* pool, StateOffs so, double* gp, const void* tab, double tau, int opening, int rowbase, const TileArgs& a, const TileGeom& tg, const GridDesc& g, hipStream_t st) {
     const int nblk = ((tg.nseg + tg.bx - 1) / tg.bx) * ((tg.nty + tg.by - 1) / tg.by) * ((tg.ntz + tg.bz - 1) / tg.bz);
     const int per_xcd = (nblk + kXcd - 1) / kXcd * tg.bx * tg.by * tg.bz;
-    hipLaunchKernelGGL((k_sweep_tile<T, K, TPB, QMAX, NT>), dim3((unsigned)(kXcd * per_xcd * a.npass)), dim3(TPB), 0, st, (T*)pool, so,
-                       (const T*)tab, a.src, a.tgt, (const T*)a.coef, rowbase, a.N, a.parity, a.npass, per_xcd, tg, g);
+    using TabT = typename std::conditional<ADJ, double, T>::type;
+    hipLaunchKernelGGL((k_sweep_tile<T, K, TPB, QMAX, NT, ADJ>), dim3((unsigned)(kXcd * per_xcd * a.npass)), dim3(TPB), 0, st, (T*)pool,
+                       so, gp, (const TabT*)tab, a.src, a.tgt, (const T*)a.coef, tau, opening, rowbase, a.N, a.parity, a.npass,
+                       per_xcd, tg, g);
 }
 
 }  // namespace
@@ -436,8 +501,10 @@ bool tile_geom(int prec, const GridDesc& g, TileGeom& tg) {
 // filled.  P39 160^3 FP64 18.3 / 17.6 / 17.1 ms at 2 / 3 / 4.  FP32 gains
 // nothing from deeper passes (64^3 0.503 / 0.512 / 0.526 / 0.502 ms at 4 / 5
 // / 8 / 10): they re-read less but keep fewer workgroups in flight.
-int tile_depth(int prec, int nd) {
-    if (nd <= 0) return 2;
+// The transpose holds three values per target: 2 degrees in FP64, 4 in FP32.
+int tile_depth(int prec, int nd, bool adj) {
+    if (nd <= 2 || (adj && prec == kF64)) return 2;
+    if (adj) return 4;
     const int kmax = prec == kF64 ? 4 : 5;
     const int np = (nd + kmax - 1) / kmax, want = (nd + np - 1) / np;
     if (want <= 2) return 2;
@@ -454,22 +521,26 @@ int tile_depth(int prec, int nd) {
 // FP32 P1 / P3 128^3, two cells per lane there, 31 / 53 vs 43 / 67).
 bool tile_use(int prec, int N, const GridDesc& g, TileGeom& tg) {
     if (N < (prec == kF64 ? 3 : 4) || !tile_geom(prec, g, tg)) return false;
-    const int nd = N / 2 + 1, K = tile_depth(prec, nd);
+    const int nd = N / 2 + 1, K = tile_depth(prec, nd, false);
     const long long nwg = (long long)tg.nseg * tg.nty * tg.ntz * ((nd + K - 1) / K);
     return nwg >= (prec == kF64 ? 320 : 1024);
 }
 
+static bool whole_lines(int prec, const TileGeom& tg, const GridDesc& g) {
+    const long long esz = prec == kF64 ? 8 : 4;
+    return g.nx * esz % 128 == 0 && (tg.whole || tg.w * esz % 128 == 0);
+}
+
 hipError_t launch_sweep_tile(int prec, void* pool, StateOffs so, const double* tab, const float* tabf, int rowbase, const TileArgs& a,
                              const TileGeom& tg, const GridDesc& g, hipStream_t st) {
-    const int esz = prec == kF64 ? 8 : 4;
-    const bool nt = g.nx * esz % 128 == 0 && (tg.whole || tg.w * esz % 128 == 0);
+    const bool nt = whole_lines(prec, tg, g);
     const void* tb = prec == kF64 ? (const void*)tab : (const void*)tabf;
-#define PM_TILE(T, KK, Q)                                                                        \
-    case KK:                                                                                     \
-        if (nt)                                                                                  \
-            launch_t<T, KK, kTpb, Q, true>(pool, so, tb, rowbase, a, tg, g, st);          \
-        else                                                                                     \
-            launch_t<T, KK, kTpb, Q, false>(pool, so, tb, rowbase, a, tg, g, st);         \
+#define PM_TILE(T, KK, Q)                                                                                        \
+    case KK:                                                                                                     \
+        if (nt)                                                                                                  \
+            launch_t<T, KK, kTpb, Q, true, false>(pool, so, nullptr, tb, 0.0, 0, rowbase, a, tg, g, st);         \
+        else                                                                                                     \
+            launch_t<T, KK, kTpb, Q, false, false>(pool, so, nullptr, tb, 0.0, 0, rowbase, a, tg, g, st);        \
         break;
     if (prec == kF64) {
         switch (a.K) {
@@ -485,6 +556,27 @@ hipError_t launch_sweep_tile(int prec, void* pool, StateOffs so, const double* t
             PM_TILE(float, 5, kQ32)
             default: return hipErrorInvalidValue;
         }
+    } else {
+        return hipErrorInvalidValue;
+    }
+#undef PM_TILE
+    return hipGetLastError();
+}
+
+hipError_t launch_adj_tile(int prec, void* pool, StateOffs so, double* gp, const double* tab, int rowbase, double tau, int opening,
+                           const TileArgs& a, const TileGeom& tg, const GridDesc& g, hipStream_t st) {
+    const bool nt = whole_lines(prec, tg, g);
+#define PM_TILE(T, KK, Q)                                                                                        \
+    if (nt)                                                                                                      \
+        launch_t<T, KK, kTpb, Q, true, true>(pool, so, gp, tab, tau, opening, rowbase, a, tg, g, st);            \
+    else                                                                                                         \
+        launch_t<T, KK, kTpb, Q, false, true>(pool, so, gp, tab, tau, opening, rowbase, a, tg, g, st);
+    if (prec == kF64 && a.K == 2) {
+        PM_TILE(double, 2, kQ64)
+    } else if (prec == kF32 && a.K == 2) {
+        PM_TILE(float, 2, kQ32)
+    } else if (prec == kF32 && a.K == 4) {
+        PM_TILE(float, 4, kQ32)
     } else {
         return hipErrorInvalidValue;
     }

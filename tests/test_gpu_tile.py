@@ -63,3 +63,64 @@ def test_tile_nonfinite_values_stay_local():
     assert bad[6, 20, 25, 64]
     z, y, x = np.nonzero(bad.any(axis=0))
     assert max(abs(z - 20).max(), abs(y - 25).max(), abs(x - 64).max()) <= 3
+
+
+@pytest.mark.parametrize("N,nx,ny,nz,nsteps,ck,prec", [
+    (3, 63, 65, 70, 7, 3, pm.PM_FP64),      # rows inside 16-byte chunks, a short last segment of steps
+    (5, 161, 45, 33, 4, 1, pm.PM_FP64),     # cut rows, every odd substep between two segments
+    (4, 64, 66, 62, 1, 5, pm.PM_FP64),      # one step: the opening half step follows the seed
+    (4, 250, 61, 36, 5, 2, pm.PM_FP32),
+    (8, 96, 75, 56, 3, 3, pm.PM_FP32)])
+def test_tile_gradient(N, nx, ny, nz, nsteps, ck, prec):
+    shape = (nz, ny, nx)
+    rng = np.random.default_rng(17 * N + nx)
+    h = 1.0 / max(shape)
+    # voids, thin and thick cells: c tau on both sides of the series switch
+    sa = rng.choice([0.0, 1e-9, 0.5, 30.0], shape)
+    ss = rng.choice([0.0, 1.0, 3.0 / h], shape)
+    q = rng.uniform(0, 1, shape)
+    u0 = rng.standard_normal(((N + 1) ** 2,) + shape).astype(np.float32).astype(np.float64)
+    tgt = rng.standard_normal(shape)
+    L, ga, gs = c_oracle.grad(N, shape, h, 0.5 * h, sa, ss, q, u0, nsteps, ck, tgt)
+    pm.pm_set_precision(prec)
+    pm.pm_init(N, nx, ny, nz, h, 0.5 * h, sa, ss, q)
+    try:
+        for i in range((N + 1) ** 2):
+            pm.pm_write(i, u0[i])
+        pm.pm_set_checkpoint(ck)
+        pm.pm_step(nsteps)
+        dsa, dss = pm.pm_grad(pm.pm_read(0) - tgt)
+    finally:
+        pm.pm_finalize()
+    e = relerr(dsa, ga), relerr(dss, gs)
+    say("tile gradient P%d %dx%dx%d prec %d: %.2e %.2e" % ((N, nx, ny, nz, prec) + e))
+    assert max(e) <= (1e-12 if prec == pm.PM_FP64 else 1e-4)
+
+
+@pytest.mark.parametrize("prec,g", [(pm.PM_FP64, None), (pm.PM_FP64, [0.5, 0.2]), (pm.PM_FP32, None)])
+def test_window_gradient_of_voids_and_thick_cells(prec, g):
+    """The window form of the transpose on the same medium, isotropic and
+    anisotropic."""
+    N, shape, nsteps, ck = 3, (6, 7, 9), 5, 2
+    rng = np.random.default_rng(5)
+    h = 0.1
+    sa = rng.choice([0.0, 1e-9, 0.5, 30.0], shape)
+    ss = rng.choice([0.0, 1.0, 3.0 / h], shape)
+    u0 = rng.standard_normal((16,) + shape).astype(np.float32).astype(np.float64)
+    tgt = rng.standard_normal(shape)
+    L, ga, gs = c_oracle.grad(N, shape, h, 0.5 * h, sa, ss, None, u0, nsteps, ck, tgt, scattering=g)
+    pm.pm_set_precision(prec)
+    pm.pm_set_scattering(g)
+    pm.pm_init(N, 9, 7, 6, h, 0.5 * h, sa, ss)
+    try:
+        for i in range(16):
+            pm.pm_write(i, u0[i])
+        pm.pm_set_checkpoint(ck)
+        pm.pm_step(nsteps)
+        dsa, dss = pm.pm_grad(pm.pm_read(0) - tgt)
+    finally:
+        pm.pm_set_scattering(None)
+        pm.pm_finalize()
+    e = relerr(dsa, ga), relerr(dss, gs)
+    say("window gradient prec %d g %s: %.2e %.2e" % ((prec, g) + e))
+    assert max(e) <= (1e-12 if prec == pm.PM_FP64 else 1e-4)
