@@ -16,21 +16,24 @@ DEVFLAGS = ["-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]
 COMMON = ["-O3", "-fPIC", "-std=c++17", "--offload-arch=" + ARCH, "-Wall",
           "-Wno-unused-result", "-I" + os.path.join(HERE, "..", "include")]
 SOURCES = [("api.cpp", False), ("flux.cpp", False), ("kernels.hip", True), ("sweep_tile.hip", True),
-           ("scratch.hip", True)]
+           ("sweep_low.hip", True), ("scratch.hip", True)]
 
 
 def build(verbose=False):
     objdir = os.path.join(HERE, "_build")
     os.makedirs(objdir, exist_ok=True)
-    objs = []
+    objs, jobs = [], []
     for name, is_hip in SOURCES:
         src = os.path.join(CSRC, name)
         obj = os.path.join(objdir, name + ".o")
         cmd = ["hipcc"] + COMMON + (["-x", "hip"] + DEVFLAGS if is_hip else []) + ["-c", src, "-o", obj]
         if verbose:
             print(" ".join(cmd), flush=True)
-        subprocess.check_call(cmd)
+        jobs.append((cmd, subprocess.Popen(cmd)))
         objs.append(obj)
+    for cmd, job in jobs:
+        if job.wait() != 0:
+            raise subprocess.CalledProcessError(job.returncode, cmd)
     tmp = LIB + ".tmp"
     cmd = ["hipcc", "-shared", "-fPIC", "--offload-arch=" + ARCH, "-o", tmp] + objs
     if verbose:

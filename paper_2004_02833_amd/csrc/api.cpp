@@ -76,6 +76,10 @@ struct Ctx {
     pm::TileGeom tg{};
     pm::TileArgs tile[2]{}, tadj[2]{};  // forward and transposed
     void* tile_mem[2] = {nullptr, nullptr};
+    bool low = false;         // forward sweeps run as low-order sweeps
+    bool low_adj = false;     // and the transposed ones
+    pm::LowArgs lowa[2]{};
+    void* low_mem = nullptr;
     double* plane64 = nullptr;
     double* red = nullptr;
     unsigned long long* redc = nullptr;
@@ -94,7 +98,12 @@ struct Ctx {
     size_t state_bytes() const { return (size_t)V * (size_t)g.pstride * esz; }
     // element offset of the first plane of a parity within a state
     long long half(int parity) const { return parity ? ve * g.pstride : 0; }
-    int passes(int parity) const { return tiled ? tile[parity].npass : win[parity].npass; }
+    int passes(int parity) const {
+        return low ? pm::low_passes(N, parity) : tiled ? tile[parity].npass : win[parity].npass;
+    }
+    int adj_passes(int parity) const {
+        return low_adj ? pm::low_passes(N, parity) : tiled ? tadj[parity].npass : wadj[parity].npass;
+    }
     hipStream_t stream() const { return g_bound ? g_bound : own; }
     void* plane(void* base, int slot) const {
         return (char*)base + (size_t)slot * (size_t)g.pstride * esz;
@@ -154,6 +163,7 @@ void release() {
     dfree(C.win_mem);
     dfree(C.tile_mem[0]);
     dfree(C.tile_mem[1]);
+    dfree(C.low_mem);
     dfree(C.halo_slots[0]);
     dfree(C.halo_slots[1]);
     dfree(C.adj_mem);
@@ -406,6 +416,64 @@ int build_tile_tables(bool adj, pm::TileArgs (&tile)[2], void** mem) {
     return PM_OK;
 }
 
+// Planes and couplings of the low-order sweep (kernels.h).
+int build_low_tables() {
+    const int N = C.N;
+    const FluxRows flux(N);
+    std::vector<double> coef[2];
+    const long long unit = C.g.pstride / 64;
+    auto exists = [&](int l, int mu, int ty) { return l >= 0 && l <= N && mu >= 0 && mu <= l && !(ty == 1 && mu == 0); };
+    auto idx = [](int l, int mu, int ty) { return l * l + l + (ty == 0 ? mu : -mu); };
+    for (int p = 0; p < 2; ++p) {  // parity of the targets
+        long long used = 0;
+        for (int l = 0; l <= N; ++l)
+            for (int k = 0; k < 2 * l + 1; ++k) {
+                const int mu = (k + 1) / 2, ty = k == 0 ? 0 : (k + 1) % 2, at = l * (l - 1) / 2 + k;
+                const int j = idx(l, mu, ty), par = l & 1;
+                const uint32_t plane = (uint32_t)((C.L.slot_of[j] - (par ? (int)C.ve : 0)) * unit);
+                if (par == p) {
+                    C.lowa[p].tgt[at] = plane;
+                    continue;
+                }
+                C.lowa[p].src[at] = plane;
+                coef[p].resize((size_t)(at + 1) * 10, 0.0);
+                const int bits = pm::grid_bits(l, ty == 0 ? mu : -mu);
+                for (int side = 0; side < 2; ++side)
+                    for (int r = 0; r < 5; ++r) {
+                        const int lt = side == 0 ? l + 1 : l - 1, tmu = r < 2 ? mu - 1 : r == 2 ? mu : mu + 1;
+                        const int tty = r == 1 || r == 4 ? 1 - ty : ty, dir = r == 2 ? 2 : r == 1 || r == 4 ? 1 : 0;
+                        const double* val = exists(lt, tmu, tty) ? flux.find(idx(lt, tmu, tty), j, dir) : nullptr;
+                        if (!val) continue;
+                        coef[p][((size_t)at * 2 + side) * 5 + r] = (((bits >> dir) & 1) ? -1.0 : 1.0) * *val / C.h[dir];
+                        ++used;
+                    }
+            }
+        if (used != flux.nnz_par[p])
+            return fail(PM_EINVAL, "internal: low-order couplings cover " + std::to_string(used) + " of " +
+                                       std::to_string(flux.nnz_par[p]));
+    }
+    const size_t es = C.prec == PM_FP64 ? sizeof(double) : sizeof(float), half = pm::kLowPlanes * 10 * sizeof(double);
+    int rc = dmalloc(&C.low_mem, 2 * half, "low-order couplings");
+    if (rc) return rc;
+    for (int p = 0; p < 2; ++p) {
+        const std::vector<float> c32(coef[p].begin(), coef[p].end());
+        const void* from = C.prec == PM_FP64 ? (const void*)coef[p].data() : (const void*)c32.data();
+        HIPCHK(hipMemcpy((char*)C.low_mem + p * half, from, coef[p].size() * es, hipMemcpyHostToDevice));
+        C.lowa[p].coef = (char*)C.low_mem + p * half;
+    }
+    return PM_OK;
+}
+
+// A forward sweep of a state in `base` on the path of the context.
+hipError_t forward(void* base, int parity, const pm::StateOffs& so, int rowbase, double tau) {
+    if (C.low)
+        return pm::launch_sweep_low(C.prec, C.N, parity, base, so, C.tab, C.tabf, rowbase, C.lowa[parity], C.g, C.stream());
+    if (C.tiled)
+        return pm::launch_sweep_tile(C.prec, base, so, C.tab, C.tabf, rowbase, C.tile[parity], C.tg, C.g, C.stream());
+    const pm::Aniso an{C.aniso ? C.gl : nullptr, tau, 0};
+    return pm::launch_sweep_win(C.prec, base, so, C.tab, C.tabf, rowbase, an, C.win[parity], C.g, C.stream());
+}
+
 // One sweep of the given parity; `full` selects tau = dt for the odd grids
 // (two merged odd half steps).
 int sweep(void* u, int parity, bool full = false) {
@@ -418,12 +486,8 @@ int sweep(void* u, int parity, bool full = false) {
     }
     const double tau = parity == 0 || full ? C.dt : 0.5 * C.dt;
     const int rowbase = parity == 0 ? 0 : full && !C.aniso ? pm::kTabOddFull : 8;
-    const pm::Aniso an{C.aniso ? C.gl : nullptr, tau, 0};
     const pm::StateOffs so{C.half(1 - parity), C.half(parity), C.half(parity), 0, 0};
-    if (C.tiled)
-        HIPCHK(pm::launch_sweep_tile(C.prec, u, so, C.tab, C.tabf, rowbase, C.tile[parity], C.tg, C.g, C.stream()));
-    else
-        HIPCHK(pm::launch_sweep_win(C.prec, u, so, C.tab, C.tabf, rowbase, an, C.win[parity], C.g, C.stream()));
+    HIPCHK(forward(u, parity, so, rowbase, tau));
     if (C.timing) {
         HIPCHK(hipEventRecord(b, C.stream()));
         C.ev[parity].push_back({a, b});
@@ -632,19 +696,25 @@ int pm_init_cells(int N, int nx, int ny, int nz, double dx, double dy, double dz
     TRY(dmalloc(&C.plane64, sizeof(double) * (size_t)ncell, "plane"));
     TRY(dmalloc(&C.red, sizeof(double) * (std::max(C.npart, C.ncheck) + 1), "reduction"));
     TRY(dmalloc(&C.redc, sizeof(unsigned long long) * (C.ncheck + 1), "reduction"));
+    C.low = !C.aniso && pm::low_use(C.prec, N, ncell);
+    C.tiled = !C.low && !C.aniso && pm::tile_use(C.prec, N, C.g, C.tg);
+    C.low_adj = C.low && N <= pm::kLowAdjMax;
     const int kwin = pm::win_depth(C.prec, nx, N, C.aniso);
-    C.tiled = !C.aniso && pm::tile_use(C.prec, N, C.g, C.tg);
-    if (C.tiled) {
+    if (C.low) {
+        TRY(build_low_tables());
+    } else if (C.tiled) {
         TRY(build_tile_tables(false, C.tile, &C.tile_mem[0]));
         TRY(build_tile_tables(true, C.tadj, &C.tile_mem[1]));
     } else {
         TRY(build_window_tables(kwin, C.win, &C.win_mem));
     }
-    if (!C.tiled && C.prec != PM_BF16 && pm::adj_depth(C.prec) != kwin) {
-        TRY(build_window_tables(pm::adj_depth(C.prec), C.wadj, &C.adj_mem));
-    } else {
-        C.wadj[0] = C.win[0];
-        C.wadj[1] = C.win[1];
+    if (C.prec != PM_BF16 && !C.low_adj && !C.tiled) {  // transposed window sweeps
+        if (C.low || pm::adj_depth(C.prec) != kwin) {
+            TRY(build_window_tables(pm::adj_depth(C.prec), C.wadj, &C.adj_mem));
+        } else {
+            C.wadj[0] = C.win[0];
+            C.wadj[1] = C.win[1];
+        }
     }
     hipStream_t s = C.stream();
     auto dev = [&](hipError_t err, const char* what) -> int {
@@ -827,8 +897,7 @@ int grad_impl(const double* dL_du0, double* dsa, double* dss, bool dev) {
             return fail(PM_EDEVICE, std::string(#x) + ": " + hipGetErrorString(e_));   \
         }                                                                              \
     } while (0)
-    const int np0 = C.tiled ? C.tadj[0].npass : C.wadj[0].npass;
-    const int np1 = C.tiled ? C.tadj[1].npass : C.wadj[1].npass;
+    const int np0 = C.adj_passes(0), np1 = C.adj_passes(1);
     const int rows = pm::grad_rows(C.aniso);
     const size_t gpb = sizeof(double) * rows * (size_t)n;  // one pass of gradient rows
     const size_t pool_bytes = C.esz * (size_t)pool_elems;
@@ -856,12 +925,7 @@ int grad_impl(const double* dL_du0, double* dsa, double* dss, bool dev) {
     auto odd_row = [&](bool full) { return full && !C.aniso ? pm::kTabOddFull : 8; };
     auto fwd = [&](int p, long long src, long long tin, long long tout, bool full) -> hipError_t {
         if (C.passes(p) == 0) return hipSuccess;  // a parity without moments (N = 0, odd)
-        const pm::Aniso an{C.aniso ? C.gl : nullptr, p ? odd_tau(full) : C.dt, 0};
-        const pm::StateOffs so{src, tin, tout, 0, 0};
-        const int row = p ? odd_row(full) : 0;
-        if (C.tiled)
-            return pm::launch_sweep_tile(C.prec, pool, so, C.tab, C.tabf, row, C.tile[p], C.tg, C.g, s);
-        return pm::launch_sweep_win(C.prec, pool, so, C.tab, C.tabf, row, an, C.win[p], C.g, s);
+        return forward(pool, p, pm::StateOffs{src, tin, tout, 0, 0}, p ? odd_row(full) : 0, p ? odd_tau(full) : C.dt);
     };
     // transpose of a substep of parity p with the target values pre and post
     auto adj = [&](int p, long long pre, long long post, bool full) -> hipError_t {
@@ -870,6 +934,8 @@ int grad_impl(const double* dL_du0, double* dsa, double* dss, bool dev) {
         const pm::StateOffs so{p ? we : wo, p ? wo : we, p ? wo : we, pre, post};
         const int row = p ? odd_row(full) : 0, opening = p && !full;
         const double tau = p ? odd_tau(full) : C.dt;
+        if (C.low_adj)
+            return pm::launch_adj_low(C.prec, C.N, p, pool, so, gp_par[p], C.tab, row, tau, opening, C.lowa[p], C.g, s);
         if (C.tiled)
             return pm::launch_adj_tile(C.prec, pool, so, gp_par[p], C.tab, row, tau, opening, C.tadj[p], C.tg, C.g, s);
         return pm::launch_adj_win(C.prec, pool, so, gp_par[p], C.tab, row, pm::Aniso{C.aniso ? C.gl : nullptr, tau, opening},

@@ -97,6 +97,27 @@ struct StateOffs {
 hipError_t launch_sweep_win(int prec, void* pool, StateOffs so, const double* tab, const float* tabf,
                             int rowbase, Aniso an, WinArgs a, GridDesc g, hipStream_t st);
 
+// Low-order sweep (see sweep_low.hip), isotropic, N <= kLowMax: planes of the
+// sources and targets of a parity (degree by degree, mu = 0 first, then cos
+// and sin of each mu) as offsets from the first plane of their parity in
+// units of 64 elements, and coef[(source * 2 + side) * 5 + r] as in the
+// window streams.
+constexpr int kLowMax = 9;
+constexpr int kLowAdjMax = 4;   // transposed sweeps (FP64 P5 overflows the registers)
+constexpr int kLowPlanes = 55;  // moments of one parity at most
+struct LowArgs {
+    uint32_t src[kLowPlanes], tgt[kLowPlanes];
+    const void* coef;
+};
+hipError_t launch_sweep_low(int prec, int N, int parity, void* pool, StateOffs so, const double* tab,
+                            const float* tabf, int rowbase, const LowArgs& a, const GridDesc& g, hipStream_t st);
+// Transposed substep, as launch_adj_win (isotropic; low_passes buffers of
+// gradient rows).
+hipError_t launch_adj_low(int prec, int N, int parity, void* pool, StateOffs so, double* gp, const double* tab,
+                          int rowbase, double tau, int opening, const LowArgs& a, const GridDesc& g, hipStream_t st);
+int low_passes(int N, int parity);
+bool low_use(int prec, int N, long long ncell);
+
 // Tile sweep (see sweep_tile.hip): boxes of w x ty x tz cells, one per
 // workgroup, nseg x nty x ntz of them; a row image takes rowch 16-byte
 // chunks, the first nmain of them the row's own cells; whole: a box holds
