@@ -41,8 +41,8 @@ __device__ __forceinline__ void wait_copies() {
 
 constexpr int kXcd = 8;
 
-template <class T, int K, int TPB, int QMAX, bool NT, bool ADJ>
-__global__ void __launch_bounds__(TPB, 4)
+template <class T, int K, int TPB, int QMAX, bool NT, bool ADJ, int WAVES>
+__global__ void __launch_bounds__(TPB, WAVES)
 k_sweep_tile(T* __restrict__ pool, StateOffs so, double* __restrict__ gp,
              const typename std::conditional<ADJ, double, T>::type* __restrict__ tab,
              const uint32_t* __restrict__ src, const uint32_t* __restrict__ tgt,
@@ -408,12 +408,12 @@ k_sweep_tile(T* __restrict__ pool, StateOffs so, double* __restrict__ gp,
     }
 }
 
-template <class T, int K, int TPB, int QMAX, bool NT, bool ADJ>
+template <class T, int K, int TPB, int QMAX, bool NT, bool ADJ, int WAVES = 4>
 void launch_t(void* pool, StateOffs so, double* gp, const void* tab, double tau, int opening, int rowbase, const TileArgs& a, const TileGeom& tg, const GridDesc& g, hipStream_t st) {
     const int nblk = ((tg.nseg + tg.bx - 1) / tg.bx) * ((tg.nty + tg.by - 1) / tg.by) * ((tg.ntz + tg.bz - 1) / tg.bz);
     const int per_xcd = (nblk + kXcd - 1) / kXcd * tg.bx * tg.by * tg.bz;
     using TabT = typename std::conditional<ADJ, double, T>::type;
-    hipLaunchKernelGGL((k_sweep_tile<T, K, TPB, QMAX, NT, ADJ>), dim3((unsigned)(kXcd * per_xcd * a.npass)), dim3(TPB), 0, st, (T*)pool,
+    hipLaunchKernelGGL((k_sweep_tile<T, K, TPB, QMAX, NT, ADJ, WAVES>), dim3((unsigned)(kXcd * per_xcd * a.npass)), dim3(TPB), 0, st, (T*)pool,
                        so, gp, (const TabT*)tab, a.src, a.tgt, (const T*)a.coef, tau, opening, rowbase, a.N, a.parity, a.npass,
                        per_xcd, tg, g);
 }
@@ -473,14 +473,16 @@ bool tile_geom(int prec, const GridDesc& g, TileGeom& tg) {
     // rows in one L2, and the eight XCDs work next to each other in every
     // plane (contiguous eighths of the grid per XCD: P39 160^3 FP64 18.3 vs
     // 17.0 ms, 64^3 0.968 vs 0.943).  The largest block that spreads the
-    // boxes within 2% of evenly, at most 64 boxes, or 16 where the grid has
-    // many (160^3 FP64: blocks of 5 / 20 / 80 boxes 16.9 / 17.2 / 18.0 ms).
+    // boxes within 2% of evenly, at most 64 boxes, or 16 and two in y where
+    // the grid has many (160^3 FP64: blocks of 5 / 20 / 80 boxes 16.9 / 17.2 /
+    // 18.0 ms; FP32 5x1x2 / 5x2x2 / 5x4x1 8.68 / 8.75 / 8.80; P19 250^3 FP32
+    // 3x1x2 / 3x2x2 / 3x4x1 9.65 / 9.64 / 9.97).
     const long long nbox = (long long)tg.nseg * tg.nty * tg.ntz;
     const int cap = nbox > 1024 ? 16 : 64;
     double most = 1e30;
     int size = 0;
-    for (int by = 8; by >= 1; by /= 2)
-        for (int bz = 8; bz >= 1; bz /= 2) {
+    for (int bz = 8; bz >= 1; bz /= 2)
+        for (int by = nbox > 1024 ? 2 : 8; by >= 1; by /= 2) {
             const int n = tg.bx * by * bz;
             if (n > cap && by * bz > 1) continue;
             const long long nblk = (long long)((tg.nseg + tg.bx - 1) / tg.bx) * ((tg.nty + by - 1) / by) * ((tg.ntz + bz - 1) / bz);
@@ -498,9 +500,11 @@ bool tile_geom(int prec, const GridDesc& g, TileGeom& tg) {
 
 // Target degrees per pass for `nd` target degrees: as few passes as the
 // registers allow (128 at two workgroups per CU: 4 degrees in FP64), evenly
-// filled.  P39 160^3 FP64 18.3 / 17.6 / 17.1 ms at 2 / 3 / 4.  FP32 gains
-// nothing from deeper passes (64^3 0.503 / 0.512 / 0.526 / 0.502 ms at 4 / 5
-// / 8 / 10): they re-read less but keep fewer workgroups in flight.
+// filled.  P39 160^3 FP64 18.3 / 17.6 / 17.1 ms at 2 / 3 / 4.  FP32 goes
+// to 5: 64^3 is the same at 4 / 5 / 8 / 10 (0.503 / 0.512 / 0.526 / 0.502 ms;
+// deeper passes re-read less but keep fewer workgroups in flight), larger
+// grids gain (P39 160^3 8.57 vs 8.45 ms at 4 / 5, P19 250^3 9.53 vs 9.19, P25
+// 97x60x133 0.828 vs 0.755).
 // The transpose holds three values per target: 2 degrees in FP64, 4 in FP32.
 int tile_depth(int prec, int nd, bool adj) {
     if (nd <= 2 || (adj && prec == kF64)) return 2;
@@ -516,14 +520,15 @@ int tile_depth(int prec, int nd, bool adj) {
 // x passes) to fill the chip with boxes of 512 cells: the window sweep's
 // smaller groups win below (FP64 240: P7 48^3 27.0 vs 30.9 us, 320: P39 32^3
 // 165 vs 162, 432: P19 48x40x36 90.7 vs 79.8; FP32 512: P7 64^3 26.7 vs
-// 28.7, 1200: P39 48^3 367 vs 240).  At low orders a pass has too few
+// 28.7, 768: P19 64x64x48 99 vs 109, 900: P19 60^3 116 vs 129, 960: P39 48^3
+// 368 vs 243, P29 64x64x40 194 vs 180).  At low orders a pass has too few
 // columns to cover its start (FP64 P1 160^3 133 vs 137, P3 128^3 125 vs 120;
 // FP32 P1 / P3 128^3, two cells per lane there, 31 / 53 vs 43 / 67).
 bool tile_use(int prec, int N, const GridDesc& g, TileGeom& tg) {
     if (N < (prec == kF64 ? 3 : 4) || !tile_geom(prec, g, tg)) return false;
     const int nd = N / 2 + 1, K = tile_depth(prec, nd, false);
     const long long nwg = (long long)tg.nseg * tg.nty * tg.ntz * ((nd + K - 1) / K);
-    return nwg >= (prec == kF64 ? 320 : 1024);
+    return nwg >= (prec == kF64 ? 320 : 950);
 }
 
 static bool whole_lines(int prec, const TileGeom& tg, const GridDesc& g) {
@@ -542,6 +547,17 @@ hipError_t launch_sweep_tile(int prec, void* pool, StateOffs so, const double* t
         else                                                                                                     \
             launch_t<T, KK, kTpb, Q, false, false>(pool, so, nullptr, tb, 0.0, 0, rowbase, a, tg, g, st);        \
         break;
+    // FP32 at depth 5 on large grids: held to 80 registers (two spilled),
+    // three workgroups fit a CU instead of two (P39 160^3 8.45 vs 8.66 ms, P19
+    // 250^3 9.19 vs 9.64); with fewer workgroups than four rounds of that, two
+    // run as well without the spills (P39 64^3 504 vs 497 us).
+    if (prec == kF32 && a.K == 5 && (long long)tg.nseg * tg.nty * tg.ntz * a.npass >= 3072) {
+        if (nt)
+            launch_t<float, 5, kTpb, kQ32, true, false, 6>(pool, so, nullptr, tb, 0.0, 0, rowbase, a, tg, g, st);
+        else
+            launch_t<float, 5, kTpb, kQ32, false, false, 6>(pool, so, nullptr, tb, 0.0, 0, rowbase, a, tg, g, st);
+        return hipGetLastError();
+    }
     if (prec == kF64) {
         switch (a.K) {
             PM_TILE(double, 2, kQ64)

@@ -50,6 +50,13 @@ def test_tile_fp32(N, nx, ny, nz):
     _run(N, (nz, ny, nx), pm.PM_FP32, 1e-6)
 
 
+@pytest.mark.parametrize("N,nx,ny,nz", [(16, 64, 112, 110), (16, 66, 112, 110)])
+def test_tile_fp32_three_workgroups_per_cu(N, nx, ny, nz):
+    """Five target degrees per pass on the smallest grids that run three
+    workgroups per CU, with whole-line rows and without."""
+    _run(N, (nz, ny, nx), pm.PM_FP32, 1e-6)
+
+
 def test_tile_nonfinite_values_stay_local():
     """An infinity reaches only the moments and cells coupled to it: empty
     source slots and idle lanes contribute nothing."""
