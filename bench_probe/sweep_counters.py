@@ -2,7 +2,7 @@
 rocprofv3 counter collection (measurement only).  The state is initialised as
 bench.py does it (the workload's moments, written from the device).
 
-    rocprofv3 --pmc FETCH_SIZE --kernel-include-regex k_sweep_win -o p -d DIR \\
+    rocprofv3 --pmc FETCH_SIZE --kernel-include-regex k_sweep -o p -d DIR \\
         -- python3 bench_probe/sweep_counters.py --workload p39_large --prec fp64
 
 A call pm_step(n) of the merged schedule launches n + 1 odd sweeps (the

@@ -208,7 +208,9 @@ int pm_cfl_warning(void);
 int pm_timing(int on);
 int pm_sweep_times(int* n_odd, double* ms_odd, int* n_even, double* ms_even);
 
-/* Release all device memory and the context.  Safe to call twice. */
+/* Release all device memory and the context, with the blocks that the
+ * library keeps for the next context (at most 1/32 of the card while a
+ * context lives).  Safe to call twice. */
 void pm_finalize(void);
 
 /* Text of the last error (static storage, never NULL). */
@@ -270,7 +272,8 @@ int pm_halo_pack(int parity, int dirs, void* device_buf);
  * ghost layers).  Queued on the bound stream.  Errors: PM_ESTATE, PM_EINVAL. */
 int pm_halo_unpack(int parity, int dirs, const void* device_buf);
 
-/* Bytes of device memory the context holds (0 without a context). */
+/* Bytes of device memory the context holds (0 without a context); blocks
+ * kept for reuse are not counted. */
 long long pm_device_bytes(void);
 
 #ifdef __cplusplus
