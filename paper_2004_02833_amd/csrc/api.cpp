@@ -824,6 +824,8 @@ int pm_init_cells(int N, int nx, int ny, int nz, double dx, double dy, double dz
         if (err == hipSuccess) return PM_OK;
         return fail(PM_EDEVICE, std::string(what) + ": " + hipGetErrorString(err));
     };
+    if (C.low) TRY(dev(pm::low_load(), "loading kernels"));
+    if (C.tiled) TRY(dev(pm::tile_load(), "loading kernels"));
     for (int p = 0; p < 2; ++p) {
         C.halo[p] = halo_plan(C.L, nx, ny, nz, p);
         TRY(dmalloc(&C.halo_slots[p], sizeof(int) * std::max<size_t>(1, C.halo[p].slots.size()), "halo faces"));

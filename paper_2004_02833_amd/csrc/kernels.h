@@ -116,6 +116,7 @@ hipError_t launch_sweep_low(int prec, int N, int parity, void* pool, StateOffs s
 hipError_t launch_adj_low(int prec, int N, int parity, void* pool, StateOffs so, double* gp, const double* tab,
                           int rowbase, double tau, int opening, const LowArgs& a, const GridDesc& g, hipStream_t st);
 int low_passes(int N, int parity);
+hipError_t low_load();   // loads the kernels' code before the first step
 bool low_use(int prec, int N, long long ncell);
 
 // Tile sweep (see sweep_tile.hip): boxes of w x ty x tz cells, one per
@@ -145,6 +146,7 @@ struct TileArgs {
 };
 bool tile_use(int prec, int N, const GridDesc& g, TileGeom& tg);  // and fills tg
 int tile_depth(int prec, int nd, bool adj);
+hipError_t tile_load();  // as low_load
 hipError_t launch_sweep_tile(int prec, void* pool, StateOffs so, const double* tab, const float* tabf,
                              int rowbase, const TileArgs& a, const TileGeom& tg, const GridDesc& g,
                              hipStream_t st);

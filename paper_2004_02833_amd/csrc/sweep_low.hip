@@ -278,6 +278,15 @@ hipError_t launch_t(int N, int parity, const LowCall& k) {
 
 int low_passes(int N, int parity) { return passes(N, parity); }
 
+// The code of a source file is loaded when one of its kernels is first used:
+// 4.4 ms inside the first step (P7 64^3 FP32; 0.08 ms with this call),
+// which may also be under stream capture.  Asking for a kernel's attributes
+// loads it while the context is made.
+hipError_t low_load() {
+    hipFuncAttributes a;
+    return hipFuncGetAttributes(&a, (const void*)k_sweep_low<double, 1, 0, false, false>);
+}
+
 // Whether the low-order sweep runs a grid of ncell cells: always where the
 // sources of a cell fit the registers of two waves per SIMD, else on grids
 // small enough for latency to decide.  Measured per sweep against the faster

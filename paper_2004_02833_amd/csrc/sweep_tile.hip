@@ -531,6 +531,11 @@ bool tile_use(int prec, int N, const GridDesc& g, TileGeom& tg) {
     return nwg >= (prec == kF64 ? 320 : 950);
 }
 
+hipError_t tile_load() {
+    hipFuncAttributes a;
+    return hipFuncGetAttributes(&a, (const void*)k_sweep_tile<double, 2, kTpb, kQ64, false, false, 4>);
+}
+
 static bool whole_lines(int prec, const TileGeom& tg, const GridDesc& g) {
     const long long esz = prec == kF64 ? 8 : 4;
     return g.nx * esz % 128 == 0 && (tg.whole || tg.w * esz % 128 == 0);
