@@ -272,6 +272,16 @@ int pm_halo_pack(int parity, int dirs, void* device_buf);
  * ghost layers).  Queued on the bound stream.  Errors: PM_ESTATE, PM_EINVAL. */
 int pm_halo_unpack(int parity, int dirs, const void* device_buf);
 
+/* Kernel that runs the sweeps of the live context, chosen by pm_init from the
+ * order, grid, storage form and scattering: forward sweeps (transposed = 0)
+ * or those of pm_grad (transposed = 1).  Results of the kernels differ by
+ * rounding only.  Returns PM_SWEEP_*, or PM_ESTATE (no context) or PM_EINVAL
+ * (another argument; transposed sweeps of bfloat16 storage). */
+#define PM_SWEEP_WINDOW 0
+#define PM_SWEEP_TILE 1
+#define PM_SWEEP_LOW 2
+int pm_sweep_kind(int transposed);
+
 /* Bytes of device memory the context holds (0 without a context); blocks
  * kept for reuse are not counted. */
 long long pm_device_bytes(void);

@@ -16,6 +16,7 @@ LIB_PATH = os.path.join(HERE, "libpm.so")
 PM_OK, PM_EINVAL, PM_ENOMEM, PM_EDEVICE, PM_ESTATE, PM_ENONFINITE = 0, -1, -2, -3, -4, -5
 PM_FP64, PM_FP32, PM_BF16 = 0, 1, 2
 PM_N_MAX = 63
+PM_SWEEP_WINDOW, PM_SWEEP_TILE, PM_SWEEP_LOW = 0, 1, 2
 
 EXPORTED = ("pm_set_precision", "pm_set_scattering", "pm_init", "pm_init_cells", "pm_write", "pm_write_dev", "pm_step", "pm_set_merge",
             "pm_read",
@@ -23,7 +24,7 @@ EXPORTED = ("pm_set_precision", "pm_set_scattering", "pm_init", "pm_init_cells",
             "pm_total", "pm_check", "pm_check_noalloc",
             "pm_bind_stream", "pm_sync", "pm_cfl_warning", "pm_timing", "pm_sweep_times",
             "pm_finalize", "pm_last_error", "pm_flux_nnz", "pm_flux_entries", "pm_moment_grid",
-            "pm_moment_slot", "pm_halo_plan", "pm_halo_pack", "pm_halo_unpack", "pm_device_bytes")
+            "pm_moment_slot", "pm_halo_plan", "pm_halo_pack", "pm_halo_unpack", "pm_sweep_kind", "pm_device_bytes")
 
 
 class PmError(RuntimeError):
@@ -80,6 +81,7 @@ def lib():
             "pm_halo_plan": ([i32, i32, i32, i32, i32, i32, P(i64), P(i64), i64], i64),
             "pm_halo_pack": ([i32, i32, vp], i32),
             "pm_halo_unpack": ([i32, i32, vp], i32),
+            "pm_sweep_kind": ([i32], i32),
             "pm_device_bytes": ([], i64),
         }
         for name, (args, res) in sig.items():
@@ -325,6 +327,10 @@ def pm_halo_pack(parity, device_ptr, dirs=7):
 
 def pm_halo_unpack(parity, device_ptr, dirs=7):
     return _check(lib().pm_halo_unpack(int(parity), int(dirs), ctypes.c_void_p(int(device_ptr))))
+
+
+def pm_sweep_kind(transposed=False):
+    return _check(lib().pm_sweep_kind(int(transposed)))
 
 
 def pm_device_bytes():

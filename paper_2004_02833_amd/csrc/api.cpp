@@ -1290,6 +1290,15 @@ int pm_halo_unpack(int parity, int dirs, const void* device_buf) {
     return halo_move(parity, dirs, const_cast<void*>(device_buf), true);
 }
 
+int pm_sweep_kind(int transposed) {
+    if (!C.live) return fail(PM_ESTATE, "no context: call pm_init first");
+    if (transposed != 0 && transposed != 1) return fail(PM_EINVAL, "pm_sweep_kind takes 0 or 1");
+    if (transposed && C.prec == PM_BF16)
+        return fail(PM_EINVAL, "gradients are not supported for bfloat16 storage");
+    if (transposed ? C.low_adj : C.low) return PM_SWEEP_LOW;
+    return C.tiled ? PM_SWEEP_TILE : PM_SWEEP_WINDOW;
+}
+
 long long pm_device_bytes(void) {
     return C.live ? C.base_bytes + (long long)C.ckpts.size() * (long long)C.state_bytes() : 0;
 }
