@@ -516,19 +516,37 @@ int tile_depth(int prec, int nd, bool adj) {
     return want <= 4 ? 4 : 5;
 }
 
-// Whether the tile sweep runs a context.  It needs enough workgroups (boxes
-// x passes) to fill the chip with boxes of 512 cells: the window sweep's
-// smaller groups win below (FP64 240: P7 48^3 27.0 vs 30.9 us, 320: P39 32^3
-// 165 vs 162, 432: P19 48x40x36 90.7 vs 79.8; FP32 512: P7 64^3 26.7 vs
-// 28.7, 768: P19 64x64x48 99 vs 109, 900: P19 60^3 116 vs 129, 960: P39 48^3
-// 368 vs 243, P29 64x64x40 194 vs 180).  At low orders a pass has too few
-// columns to cover its start (FP64 P1 160^3 133 vs 137, P3 128^3 125 vs 120;
-// FP32 P1 / P3 128^3, two cells per lane there, 31 / 53 vs 43 / 67).
+// Whether the tile sweep runs a context that the low-order sweep does not take
+// (FP64 from P5, FP32 from P8 on).  Measured per sweep, window / tile in us:
+// - It needs enough workgroups (boxes x passes) to fill the chip with boxes of
+//   512 cells; the window sweep's smaller groups win below (FP64 240: P7 48^3
+//   27.0 / 30.9, 432: P19 48x40x36 90.7 / 79.8; FP32 768: P19 64x64x48 99 /
+//   109, 900: P19 60^3 116 / 129, 960: P39 48^3 368 / 243).
+// - Boxes with most lanes idle copy more padding than values: rows of one
+//   cell, half the lanes idle and more (FP64 P7 1x512x512 53 / 79, 1x1x400000
+//   78 / 388; FP32 P12 2x512x512 110 / 261), FP32 up to 0.7 of them busy (P12
+//   5x300x300 0.71 of the window's speed, 5x600x600 0.84).
+// - FP32 rows of up to 64 cells are contiguous in the window sweep's linear
+//   tiles, and on planes that start on cache lines its chunks are whole lines;
+//   there the tile sweep gains only from 3072 boxes on, or as many workgroups
+//   from P14 on (P12 20x130x97 0.91, P19 33x90x61 0.80, 56^3 0.76 of its
+//   speed, 40x200x200 1.03 and 1.13; P9 96^3 0.87, 66x128x100 0.79,
+//   66x200x200 1.13).  Rows of 16, 32 and 48 cells and boxes with their lanes
+//   filled stay (P12 48x80x80 1.79, 128x64x64 1.11).
+// - Rows longer than 64 cells with fewer than four planes leave three of four
+//   window waves idle (P12 512x512x1 2.5 times the window's speed).
 bool tile_use(int prec, int N, const GridDesc& g, TileGeom& tg) {
-    if (N < (prec == kF64 ? 3 : 4) || !tile_geom(prec, g, tg)) return false;
+    if (!tile_geom(prec, g, tg)) return false;
     const int nd = N / 2 + 1, K = tile_depth(prec, nd, false);
-    const long long nwg = (long long)tg.nseg * tg.nty * tg.ntz * ((nd + K - 1) / K);
-    return nwg >= (prec == kF64 ? 320 : 950);
+    const long long boxes = (long long)tg.nseg * tg.nty * tg.ntz, nwg = boxes * ((nd + K - 1) / K);
+    const double util = (double)g.ncell / ((double)boxes * kTpb);
+    if (nwg < (prec == kF64 ? 320 : 950) || util <= 0.5) return false;
+    if (prec == kF64 || (g.nz < 4 && g.nx > 64)) return true;
+    if (util < 0.7) return false;
+    const bool few = boxes < 3072 && (N < 14 || nwg < 3072);
+    if (few && g.nx < 64 && g.nx % 16) return false;
+    const bool planes_on_lines = (long long)g.nx * g.ny * 4 % 128 == 0;
+    return !(few && N < 14 && util < 0.8 && planes_on_lines);
 }
 
 hipError_t tile_load() {
