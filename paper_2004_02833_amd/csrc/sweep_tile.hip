@@ -464,7 +464,7 @@ bool tile_geom(int prec, const GridDesc& g, TileGeom& tg) {
                 const double cost = (1.0 + halo) * (0.75 + 0.25 / util) * (1.0 + (rows_fit ? 45.0 : 70.0) / run);
                 if (cost < best) {
                     best = cost;
-                    tg = TileGeom{W, TY, TZ, nseg, nty, ntz, rowch, nmain, whole ? 1 : 0, nseg < 8 ? nseg : 8, 1, 1};
+                    tg = TileGeom{W, TY, TZ, nseg, nty, ntz, rowch, nmain, whole ? 1 : 0, 1, 1, 1};
                 }
             }
     }
@@ -476,7 +476,13 @@ bool tile_geom(int prec, const GridDesc& g, TileGeom& tg) {
     // boxes within 2% of evenly, at most 64 boxes, or 16 and two in y where
     // the grid has many (160^3 FP64: blocks of 5 / 20 / 80 boxes 16.9 / 17.2 /
     // 18.0 ms; FP32 5x1x2 / 5x2x2 / 5x4x1 8.68 / 8.75 / 8.80; P19 250^3 FP32
-    // 3x1x2 / 3x2x2 / 3x4x1 9.65 / 9.64 / 9.97).
+    // 3x1x2 / 3x2x2 / 3x4x1 9.65 / 9.64 / 9.97).  More than eight segments go
+    // in the blocks of five to eight that leave the fewest empty places: 9 as
+    // 8 + 1 gave every other XCD one box to eight (P12 540x40x40 FP64 604 us
+    // a sweep, as 5 + 4 457; window 469).
+    tg.bx = tg.nseg < 8 ? tg.nseg : 8;
+    for (int b = 7; tg.nseg > 8 && b >= 5; --b)
+        if ((tg.nseg + b - 1) / b * b < (tg.nseg + tg.bx - 1) / tg.bx * tg.bx) tg.bx = b;
     const long long nbox = (long long)tg.nseg * tg.nty * tg.ntz;
     const int cap = nbox > 1024 ? 16 : 64;
     double most = 1e30;
