@@ -539,6 +539,11 @@ int tile_depth(int prec, int nd, bool adj) {
 //   speed, 40x200x200 1.03 and 1.13; P9 96^3 0.87, 66x128x100 0.79,
 //   66x200x200 1.13).  Rows of 16, 32 and 48 cells and boxes with their lanes
 //   filled stay (P12 48x80x80 1.79, 128x64x64 1.11).
+// - Ten odd degrees are three FP64 passes, 4 + 4 + 2: with 257 to 344 boxes the
+//   first two run over the 512 workgroups that fit at a time and the rest
+//   cannot fill a second round (P19 36x60x60, 270 boxes, 0.92 of the window's
+//   speed, 50x50x56, 280, 0.89, 30x70x70, 324, 0.92; 50^3, 250, 1.04 and
+//   56^3, 361, 1.01; P18 and P21 gain there).
 // - Rows longer than 64 cells with fewer than four planes leave three of four
 //   window waves idle (P12 512x512x1 2.5 times the window's speed).
 bool tile_use(int prec, int N, const GridDesc& g, TileGeom& tg) {
@@ -547,7 +552,8 @@ bool tile_use(int prec, int N, const GridDesc& g, TileGeom& tg) {
     const long long boxes = (long long)tg.nseg * tg.nty * tg.ntz, nwg = boxes * ((nd + K - 1) / K);
     const double util = (double)g.ncell / ((double)boxes * kTpb);
     if (nwg < (prec == kF64 ? 320 : 950) || util <= 0.5) return false;
-    if (prec == kF64 || (g.nz < 4 && g.nx > 64)) return true;
+    if (prec == kF64) return !((N + 1) / 2 == 10 && boxes > 256 && boxes < 345 && g.nx <= 64);
+    if (g.nz < 4 && g.nx > 64) return true;
     if (util < 0.7) return false;
     const bool few = boxes < 3072 && (N < 14 || nwg < 3072);
     if (few && g.nx < 64 && g.nx % 16) return false;
