@@ -73,6 +73,7 @@ struct Ctx {
     pm::WinArgs win[2]{};     // forward sweeps
     pm::WinArgs wadj[2]{};    // transposed sweeps (pm_grad)
     bool tiled = false;       // forward sweeps run as tile sweeps
+    bool tiled_adj = false;   // and the transposed ones
     pm::TileGeom tg{};
     pm::TileArgs tile[2]{}, tadj[2]{};  // forward and transposed
     void* tile_mem[2] = {nullptr, nullptr};
@@ -102,7 +103,7 @@ struct Ctx {
         return low ? pm::low_passes(N, parity) : tiled ? tile[parity].npass : win[parity].npass;
     }
     int adj_passes(int parity) const {
-        return low_adj ? pm::low_passes(N, parity) : tiled ? tadj[parity].npass : wadj[parity].npass;
+        return low_adj ? pm::low_passes(N, parity) : tiled_adj ? tadj[parity].npass : wadj[parity].npass;
     }
     hipStream_t stream() const { return g_bound ? g_bound : own; }
     void* plane(void* base, int slot) const {
@@ -802,16 +803,18 @@ int pm_init_cells(int N, int nx, int ny, int nz, double dx, double dy, double dz
     C.low = !C.aniso && pm::low_use(C.prec, N, ncell);
     C.tiled = !C.low && !C.aniso && pm::tile_use(C.prec, N, C.g, C.tg);
     C.low_adj = C.low && N <= pm::kLowAdjMax;
+    C.tiled_adj = C.tiled || (C.low && !C.low_adj && C.prec != PM_BF16 && pm::tile_use_adj(C.prec, N, C.g, C.tg));
     const int kwin = pm::win_depth(C.prec, nx, N, C.aniso);
     if (C.low) {
         TRY(build_low_tables());
     } else if (C.tiled) {
         TRY(build_tile_tables(false, C.tile, &C.tile_mem[0]));
-        TRY(build_tile_tables(true, C.tadj, &C.tile_mem[1]));
     } else {
         TRY(build_window_tables(kwin, C.win, &C.win_mem));
     }
-    if (C.prec != PM_BF16 && !C.low_adj && !C.tiled) {  // transposed window sweeps
+    if (C.tiled_adj) {
+        TRY(build_tile_tables(true, C.tadj, &C.tile_mem[1]));
+    } else if (C.prec != PM_BF16 && !C.low_adj) {  // transposed window sweeps
         if (C.low || pm::adj_depth(C.prec) != kwin) {
             TRY(build_window_tables(pm::adj_depth(C.prec), C.wadj, &C.adj_mem));
         } else {
@@ -825,7 +828,7 @@ int pm_init_cells(int N, int nx, int ny, int nz, double dx, double dy, double dz
         return fail(PM_EDEVICE, std::string(what) + ": " + hipGetErrorString(err));
     };
     if (C.low) TRY(dev(pm::low_load(), "loading kernels"));
-    if (C.tiled) TRY(dev(pm::tile_load(), "loading kernels"));
+    if (C.tiled_adj) TRY(dev(pm::tile_load(), "loading kernels"));
     for (int p = 0; p < 2; ++p) {
         C.halo[p] = halo_plan(C.L, nx, ny, nz, p);
         TRY(dmalloc(&C.halo_slots[p], sizeof(int) * std::max<size_t>(1, C.halo[p].slots.size()), "halo faces"));
@@ -1044,7 +1047,7 @@ int grad_impl(const double* dL_du0, double* dsa, double* dss, bool dev) {
         const double tau = p ? odd_tau(full) : C.dt;
         if (C.low_adj)
             return pm::launch_adj_low(C.prec, C.N, p, pool, so, gp_par[p], C.tab, row, tau, opening, C.lowa[p], C.g, s);
-        if (C.tiled)
+        if (C.tiled_adj)
             return pm::launch_adj_tile(C.prec, pool, so, gp_par[p], C.tab, row, tau, opening, C.tadj[p], C.tg, C.g, s);
         return pm::launch_adj_win(C.prec, pool, so, gp_par[p], C.tab, row, pm::Aniso{C.aniso ? C.gl : nullptr, tau, opening},
                                   C.wadj[p], C.g, s);
@@ -1296,7 +1299,7 @@ int pm_sweep_kind(int transposed) {
     if (transposed && C.prec == PM_BF16)
         return fail(PM_EINVAL, "gradients are not supported for bfloat16 storage");
     if (transposed ? C.low_adj : C.low) return PM_SWEEP_LOW;
-    return C.tiled ? PM_SWEEP_TILE : PM_SWEEP_WINDOW;
+    return (transposed ? C.tiled_adj : C.tiled) ? PM_SWEEP_TILE : PM_SWEEP_WINDOW;
 }
 
 long long pm_device_bytes(void) {

@@ -144,7 +144,8 @@ struct TileArgs {
     const uint32_t* tgt;
     const void* coef;
 };
-bool tile_use(int prec, int N, const GridDesc& g, TileGeom& tg);  // and fills tg
+bool tile_use(int prec, int N, const GridDesc& g, TileGeom& tg);      // and fills tg
+bool tile_use_adj(int prec, int N, const GridDesc& g, TileGeom& tg);  // transpose of a low-order context
 int tile_depth(int prec, int nd, bool adj);
 hipError_t tile_load();  // as low_load
 hipError_t launch_sweep_tile(int prec, void* pool, StateOffs so, const double* tab, const float* tabf,

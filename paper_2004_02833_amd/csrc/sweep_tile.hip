@@ -561,6 +561,24 @@ bool tile_use(int prec, int N, const GridDesc& g, TileGeom& tg) {
     return !(few && N < 14 && util < 0.8 && planes_on_lines);
 }
 
+// Whether the transpose of a low-order context above P4 (where that sweep has
+// none) runs as a tile sweep, and not as a window sweep.  Whole reverse passes,
+// window / tile: FP64 gains where the window's accesses are short or cross
+// rows, from 320 boxes on (P5 64^3 1.13, 161x45x33 1.14, P6 32x80x80 1.13; but P5
+// 56^3 0.95, 33x90x61 0.96).  FP32 runs four degrees in one pass, so
+// the boxes must fill their rounds of 512 (P7 128x64x64, 1024 boxes, 1.43, 60^3,
+// 450, 1.12, 97x60x133, 2010, 1.26; 20x130x97, 520, 0.85, 33x130x111, 1064,
+// 0.93), with most lanes busy (P5 5x200x200 0.84).
+bool tile_use_adj(int prec, int N, const GridDesc& g, TileGeom& tg) {
+    if (N <= kLowAdjMax || !tile_geom(prec, g, tg)) return false;
+    const long long boxes = (long long)tg.nseg * tg.nty * tg.ntz;
+    const double util = (double)g.ncell / ((double)boxes * kTpb);
+    if (prec == kF64) return boxes >= 320 && util > 0.5 && (g.nx % 16 == 0 || g.nx > 64);
+    const int nd = N / 2 + 1, K = tile_depth(prec, nd, true);
+    const long long nwg = boxes * ((nd + K - 1) / K);
+    return util > 0.7 && (double)nwg >= 0.7 * (double)((nwg + 511) / 512 * 512);
+}
+
 hipError_t tile_load() {
     hipFuncAttributes a;
     return hipFuncGetAttributes(&a, (const void*)k_sweep_tile<double, 2, kTpb, kQ64, false, false, 4>);
