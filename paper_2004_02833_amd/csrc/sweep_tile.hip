@@ -547,7 +547,7 @@ int tile_depth(int prec, int nd, bool adj) {
 // - Rows longer than 64 cells with fewer than four planes leave three of four
 //   window waves idle (P12 512x512x1 2.5 times the window's speed).
 bool tile_use(int prec, int N, const GridDesc& g, TileGeom& tg) {
-    if (!tile_geom(prec, g, tg)) return false;
+    if (N < 5 || !tile_geom(prec, g, tg)) return false;  // P0 comes here too: no dual moments
     const int nd = N / 2 + 1, K = tile_depth(prec, nd, false);
     const long long boxes = (long long)tg.nseg * tg.nty * tg.ntz, nwg = boxes * ((nd + K - 1) / K);
     const double util = (double)g.ncell / ((double)boxes * kTpb);

@@ -36,6 +36,8 @@ def _kinds(prec, N, nx, ny, nz):
     # low orders, small grids
     (pm.PM_FP64, 4, 64, 64, 64, L), (pm.PM_FP32, 7, 64, 64, 64, L), (pm.PM_BF16, 6, 64, 64, 64, L), (pm.PM_BF16, 10, 64, 64, 64, W),
     (pm.PM_FP64, 12, 30, 30, 30, W), (pm.PM_FP64, 12, 64, 64, 64, T), (pm.PM_FP64, 19, 701, 20, 20, T),
+    # P0 has no dual moments
+    (pm.PM_FP64, 0, 64, 64, 64, W), (pm.PM_FP32, 0, 128, 128, 128, W),
     # FP64 passes that just overflow the chip
     (pm.PM_FP64, 19, 30, 70, 70, W), (pm.PM_FP64, 19, 50, 50, 50, T), (pm.PM_FP64, 19, 56, 56, 56, T), (pm.PM_FP64, 21, 30, 70, 70, T)])
 def test_forward_kernel(prec, N, nx, ny, nz, kind):
