@@ -512,14 +512,12 @@ bool tile_geom(int prec, const GridDesc& g, TileGeom& tg) {
 // grids gain (P39 160^3 8.57 vs 8.45 ms at 4 / 5, P19 250^3 9.53 vs 9.19, P25
 // 97x60x133 0.828 vs 0.755).
 // The transpose holds three values per target: 2 degrees in FP64, 4 in FP32.
+// Contexts have nd >= 3 (P5 on), so FP64 passes take 3 or 4.
 int tile_depth(int prec, int nd, bool adj) {
-    if (nd <= 2 || (adj && prec == kF64)) return 2;
-    if (adj) return 4;
+    if (adj) return prec == kF64 ? 2 : 4;
     const int kmax = prec == kF64 ? 4 : 5;
     const int np = (nd + kmax - 1) / kmax, want = (nd + np - 1) / np;
-    if (want <= 2) return 2;
-    if (prec == kF64) return want;
-    return want <= 4 ? 4 : 5;
+    return prec == kF64 ? want : want <= 4 ? 4 : 5;
 }
 
 // Whether the tile sweep runs a context that the low-order sweep does not take
@@ -581,7 +579,7 @@ bool tile_use_adj(int prec, int N, const GridDesc& g, TileGeom& tg) {
 
 hipError_t tile_load() {
     hipFuncAttributes a;
-    return hipFuncGetAttributes(&a, (const void*)k_sweep_tile<double, 2, kTpb, kQ64, false, false, 4>);
+    return hipFuncGetAttributes(&a, (const void*)k_sweep_tile<double, 4, kTpb, kQ64, true, false, 4>);
 }
 
 static bool whole_lines(int prec, const TileGeom& tg, const GridDesc& g) {
@@ -613,14 +611,12 @@ hipError_t launch_sweep_tile(int prec, void* pool, StateOffs so, const double* t
     }
     if (prec == kF64) {
         switch (a.K) {
-            PM_TILE(double, 2, kQ64)
             PM_TILE(double, 3, kQ64)
             PM_TILE(double, 4, kQ64)
             default: return hipErrorInvalidValue;
         }
     } else if (prec == kF32) {
         switch (a.K) {
-            PM_TILE(float, 2, kQ32)
             PM_TILE(float, 4, kQ32)
             PM_TILE(float, 5, kQ32)
             default: return hipErrorInvalidValue;
@@ -642,8 +638,6 @@ hipError_t launch_adj_tile(int prec, void* pool, StateOffs so, double* gp, const
         launch_t<T, KK, kTpb, Q, false, true>(pool, so, gp, tab, tau, opening, rowbase, a, tg, g, st);
     if (prec == kF64 && a.K == 2) {
         PM_TILE(double, 2, kQ64)
-    } else if (prec == kF32 && a.K == 2) {
-        PM_TILE(float, 2, kQ32)
     } else if (prec == kF32 && a.K == 4) {
         PM_TILE(float, 4, kQ32)
     } else {
