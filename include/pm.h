@@ -87,6 +87,10 @@ int pm_set_scattering(const double* g, int count);
  * state starts at zero.  dt above the stability limit dx / (sqrt(3) *
  * lambda_max(N)) only sets a warning (pm_cfl_warning): the paper notes that
  * scattering can stabilise larger steps (Sec. 2.1, last paragraph).
+ * Device memory freed here, by pm_grad and by a dropped recording is kept for
+ * the next allocation of its size: at most 1/32 of the card and 1/8 of what
+ * is free on it at the time.  Other allocators of the process do not see it;
+ * pm_finalize gives it back.
  * Errors: PM_EINVAL, PM_ENOMEM, PM_EDEVICE. */
 int pm_init(int N, int nx, int ny, int nz, double dx, double dt,
             const double* sigma_a, const double* sigma_s, const double* q);
@@ -148,8 +152,9 @@ int pm_set_checkpoint(int k);
  * discrete step).  Input: host dL/du_0 at the final time (nx*ny*nz; the
  * other moments get a zero cotangent).  Output: host dL/dsigma_a and
  * dL/dsigma_s, cell-centred (either may be NULL).  The forward state is left
- * unchanged.  Errors: PM_ESTATE (no recording), PM_EINVAL, PM_ENOMEM,
- * PM_EDEVICE. */
+ * unchanged.  Its temporaries (about k + 1 states at checkpoints every k
+ * steps) are freed, but may be kept by the library (see pm_init).  Errors:
+ * PM_ESTATE (no recording), PM_EINVAL, PM_ENOMEM, PM_EDEVICE. */
 int pm_grad(const double* dL_du0, double* dsigma_a, double* dsigma_s);
 
 /* Same with device pointers: dL_du0 holds nx*ny*nz float64 values on the
@@ -209,8 +214,7 @@ int pm_timing(int on);
 int pm_sweep_times(int* n_odd, double* ms_odd, int* n_even, double* ms_even);
 
 /* Release all device memory and the context, with the blocks that the
- * library keeps for the next context (at most 1/32 of the card while a
- * context lives).  Safe to call twice. */
+ * library keeps for the next context (see pm_init).  Safe to call twice. */
 void pm_finalize(void);
 
 /* Text of the last error (static storage, never NULL). */

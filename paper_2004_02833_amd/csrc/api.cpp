@@ -119,9 +119,10 @@ Ctx C;
 // to the driver are wiped before it hands them out again (P7 64^3, 100
 // recorded steps: a forward and gradient 41 ms on a fresh device, 140 ms
 // after large contexts).  While a context is replaced its blocks wait for the
-// new one; afterwards at most 1/32 of the device's memory stays, all of it is
-// given back when an allocation fails and by pm_finalize, and the checks of
-// free memory count it as free.
+// new one; afterwards at most 1/32 of the device's memory stays, and at most
+// 1/8 of what is free there, since other users of the card cannot ask for it;
+// all of it is given back when an allocation fails here and by pm_finalize, and
+// the checks of free memory count it as free.
 struct Block {
     void* p;
     size_t bytes;
@@ -147,19 +148,20 @@ void trim_kept(size_t most) {
     }
 }
 
-void trim_kept_to_share() {
-    size_t fr = 0, tot = 0;
-    if (!g_kept.empty() && hipMemGetInfo(&fr, &tot) == hipSuccess) trim_kept(tot / 32);
-}
-
 // hipMemGetInfo with the kept blocks of this device counted as free.
-hipError_t free_memory(size_t* fr) {
+hipError_t free_memory(size_t* fr, size_t* total = nullptr) {
     size_t tot = 0;
     const hipError_t e = hipMemGetInfo(fr, &tot);
     if (e == hipSuccess)
         for (const Block& b : g_kept)
             if (b.dev == this_device()) *fr += b.bytes;
+    if (total) *total = tot;
     return e;
+}
+
+void trim_kept_to_share() {
+    size_t fr = 0, tot = 0;
+    if (!g_kept.empty() && free_memory(&fr, &tot) == hipSuccess) trim_kept(std::min(tot / 32, fr / 8));
 }
 
 template <class P>

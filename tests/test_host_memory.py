@@ -1,0 +1,59 @@
+"""The library's host side on a CPU stand-in for the HIP runtime (fake_hip.cpp):
+what stays allocated between contexts, and which device is waited for."""
+import ctypes
+import os
+import subprocess
+
+import numpy as np
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+CSRC = os.path.join(ROOT, "paper_2004_02833_amd", "csrc")
+GB = 1 << 30
+N, EDGE = 3, 128                      # 16 moments of 128^3 cells
+CELLS = EDGE ** 3
+STATE = 16 * (CELLS + 64) * 8         # planes padded off the power of two
+
+
+@pytest.fixture(scope="module")
+def host(tmp_path_factory):
+    so = str(tmp_path_factory.mktemp("fake") / "libpm_host.so")
+    subprocess.run(["g++", "-std=c++17", "-O1", "-shared", "-fPIC", "-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include",
+                    "-I" + os.path.join(ROOT, "include"), "-I" + CSRC, os.path.join(CSRC, "api.cpp"), os.path.join(CSRC, "flux.cpp"),
+                    os.path.join(ROOT, "tests", "fake_hip.cpp"), "-o", so], check=True)
+    L = ctypes.CDLL(so)
+    L.fake_live.restype = L.pm_device_bytes.restype = ctypes.c_longlong
+    L.fake_reset.argtypes = [ctypes.c_longlong]
+    L.fake_others.argtypes = [ctypes.c_int, ctypes.c_longlong]
+    L.pm_init.argtypes = [ctypes.c_int] * 4 + [ctypes.c_double] * 2 + [ctypes.POINTER(ctypes.c_double)] * 3
+    yield L
+    L.pm_finalize()
+
+
+FIELD = np.full(CELLS, 0.5)
+
+
+def _init(L, edge=EDGE):
+    p = FIELD.ctypes.data_as(ctypes.POINTER(ctypes.c_double))
+    assert L.pm_init(N, edge, edge, edge, 1.0 / edge, 0.5 / edge, p, p, None) == 0
+
+
+@pytest.mark.parametrize("free", [12 * GB, 40 * GB, 288 * GB])
+def test_kept_memory_is_a_share_of_the_free_memory(host, free):
+    """A dropped recording of 20 states stays for the next one, but at most an
+    eighth of what the card has free and 1/32 of the card."""
+    host.fake_reset(288 * GB)
+    host.fake_others(0, 288 * GB - free)
+    try:
+        _init(host)
+        context = host.fake_live(0)
+        assert host.pm_set_checkpoint(1) == 0 and host.pm_step(20) == 0
+        assert host.fake_live(0) >= context + 20 * STATE
+        assert host.pm_set_checkpoint(0) == 0
+        kept = host.fake_live(0) - host.pm_device_bytes()
+        share = min((free - host.pm_device_bytes()) // 8, 9 * GB)
+        assert kept <= share
+        assert kept > min(20 * STATE, share) - 2 * STATE
+    finally:
+        host.pm_finalize()
+    assert host.fake_live(0) == 0
