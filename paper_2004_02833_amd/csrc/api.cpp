@@ -51,6 +51,7 @@ struct HaloPlan {
 
 struct Ctx {
     bool live = false;
+    int dev = -1;  // device of its memory and stream
     int N = 0, V = 0, nx = 0, ny = 0, nz = 0;
     long long ncell = 0;
     double h[3] = {0, 0, 0};  // cell edges dx, dy, dz
@@ -197,7 +198,8 @@ int dmalloc(P** p, size_t bytes, const char* what) {
     return PM_OK;
 }
 
-// The caller has waited for the work that uses the block (as hipFree would).
+// The caller has waited for the work that uses the block (wait_context: as
+// hipFree would).
 void dfree(void* p) {
     if (!p) return;
     for (size_t i = g_used.size(); i-- > 0;)
@@ -206,6 +208,16 @@ void dfree(void* p) {
             g_used.erase(g_used.begin() + (long)i);
             return;
         }
+}
+
+// Waits for everything queued on the context's device, which need not be the
+// current one.
+void wait_context() {
+    const int dev = this_device();
+    const bool other = C.dev >= 0 && C.dev != dev;
+    if (other) (void)hipSetDevice(C.dev);
+    (void)hipDeviceSynchronize();
+    if (other) (void)hipSetDevice(dev);
 }
 
 // The library's own stream, kept from context to context on a device.
@@ -236,7 +248,7 @@ long long g_rec_id = 1;
 
 void drop_recording(bool replacing = false) {
     if (!C.ckpts.empty()) {
-        if (!replacing) (void)hipDeviceSynchronize();
+        if (!replacing) wait_context();
         for (void* p : C.ckpts) dfree(p);
         C.ckpts.clear();
         if (!replacing) trim_kept_to_share();
@@ -256,7 +268,7 @@ void drop_events() {
 }
 
 void release() {
-    if (C.u || C.tab) (void)hipDeviceSynchronize();
+    if (C.u || C.tab) wait_context();
     drop_recording(true);
     drop_events();
     dfree(C.u);
@@ -730,6 +742,7 @@ int pm_init_cells(int N, int nx, int ny, int nz, double dx, double dy, double dz
             if (!std::isfinite(q[i])) return fail(PM_EINVAL, "q[" + std::to_string(i) + "] not finite");
 
     release();
+    C.dev = this_device();
     C.N = N;
     C.V = (N + 1) * (N + 1);
     C.nx = nx;

@@ -57,3 +57,28 @@ def test_kept_memory_is_a_share_of_the_free_memory(host, free):
     finally:
         host.pm_finalize()
     assert host.fake_live(0) == 0
+
+
+@pytest.mark.parametrize("replace", [False, True])
+def test_work_on_freed_blocks_is_waited_for_on_their_device(host, replace):
+    """A recording or a context given up while another device is current: its
+    blocks may be handed out again, so the work on them is waited for where it
+    runs, and the caller's device stays current."""
+    host.fake_reset(288 * GB)
+    try:
+        _init(host)
+        assert host.pm_set_checkpoint(1) == 0 and host.pm_step(3) == 0
+        assert host.fake_busy(0)
+        host.hipSetDevice(1)
+        if replace:
+            _init(host, edge=16)
+            assert host.fake_live(1) > 0
+        else:
+            assert host.pm_set_checkpoint(0) == 0
+        assert not host.fake_busy(0)
+        dev = ctypes.c_int(-1)
+        host.hipGetDevice(ctypes.byref(dev))
+        assert dev.value == 1
+    finally:
+        host.pm_finalize()
+    assert host.fake_live(0) == host.fake_live(1) == 0
