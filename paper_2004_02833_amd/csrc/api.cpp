@@ -64,7 +64,7 @@ struct Ctx {
     void* u = nullptr;
     double* tab = nullptr;
     float* tabf = nullptr;  // float copy for the FP32 update (float/bfloat16 storage, isotropic)
-    double* sig = nullptr;  // sigma_a, sigma_s (device copies)
+    double* sig = nullptr;  // sigma_a, sigma_s on the device, until the tables are made
     bool aniso = false;     // some g_l != 0 for 1 <= l <= N
     double* gl = nullptr;   // g_0 .. g_N on the device (anisotropic scattering)
     void* win_mem = nullptr;  // window sweep streams (both parities)
@@ -864,6 +864,9 @@ int pm_init_cells(int N, int nx, int ny, int nz, double dx, double dy, double dz
     TRY(dev(pm::launch_fill_zero(C.u, (long long)C.state_bytes(), s), "zero state"));
     TRY(dev(hipStreamSynchronize(s), "sync"));
 #undef TRY
+    dfree(C.sig);
+    C.sig = nullptr;
+    C.dev_bytes -= (long long)(sizeof(double) * 2 * (size_t)ncell);
     trim_kept_to_share();
     C.base_bytes = C.dev_bytes;
     C.live = true;

@@ -82,3 +82,17 @@ def test_work_on_freed_blocks_is_waited_for_on_their_device(host, replace):
     finally:
         host.pm_finalize()
     assert host.fake_live(0) == host.fake_live(1) == 0
+
+
+@pytest.mark.parametrize("prec,tables", [(0, 27 * 8), (1, 27 * 12)])
+def test_a_context_holds_no_medium_after_its_tables(host, prec, tables):
+    """State, tables and one float64 plane, and less than 1 MB beside them: the
+    copies of sigma_a and sigma_s are needed for the tables only."""
+    host.fake_reset(288 * GB)
+    assert host.pm_set_precision(prec) == 0
+    try:
+        _init(host)
+        assert host.pm_device_bytes() < STATE // (1 + prec) + CELLS * (tables + 8) + (1 << 20)
+    finally:
+        host.pm_set_precision(0)
+        host.pm_finalize()
