@@ -26,8 +26,11 @@ namespace pm {
 namespace {
 
 // 64 lanes x 16 bytes from base + voff (per lane) to LDS at ldsaddr + 16 lane.
-// No register is written; completion is waited for with vmcnt.  M0, the LDS
-// address, has no other use in these kernels.
+// No register receives data; completion is waited for with vmcnt.  M0 is the
+// LDS address.  It is a reserved register, which the compiler does not take in
+// a clobber list and sets before uses of its own (indexed registers,
+// messages); these kernels have none, so every s_mov to M0 in their code is
+// this one.
 __device__ __forceinline__ void copy16(uint32_t voff, uint64_t base, uint32_t ldsaddr) {
     asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1"
                  :
