@@ -10,6 +10,7 @@
 
 #include <algorithm>
 #include <cmath>
+#include <cstdint>
 #include <cstdio>
 #include <cstring>
 #include <string>
@@ -1073,7 +1074,9 @@ int grad_impl(const double* dL_du0, double* dsa, double* dss, bool dev) {
     const long long nseg = (T + ck - 1) / ck;
     for (long long gseg = nseg - 1; gseg >= 0; --gseg) {
         const long long s0 = gseg * ck, len = std::min<long long>(s0 + ck, T) - s0;
-        const long long E0 = ((char*)C.ckpts[gseg] - (char*)pool) / (long long)C.esz, O0 = E0 + EH;
+        // the checkpoint's place as an offset from the pool: a difference of
+        // addresses (two allocations; both on 256 bytes, so whole elements)
+        const long long E0 = ((long long)(intptr_t)C.ckpts[gseg] - (long long)(intptr_t)pool) / (long long)C.esz, O0 = E0 + EH;
         auto P = [&](long long g) { return P0 + (g & 1) * OH; };
         auto E = [&](long long j) { return j == 0 ? E0 : EB + (j - 1) * EH; };
         auto O1 = [&](long long j) { return j == 0 ? P(gseg) : OB + (j - 1) * OH; };
