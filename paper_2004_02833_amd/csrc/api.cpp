@@ -130,7 +130,8 @@ struct Block {
     size_t bytes;
     int dev;
 };
-std::vector<Block> g_used, g_kept;
+std::vector<Block> g_used, g_kept;  // g_kept: the longest kept first
+constexpr size_t kKeptBlocks = 256;  // searched one by one
 
 int this_device() {
     int d = 0;
@@ -138,25 +139,38 @@ int this_device() {
     return d;
 }
 
-// Gives kept blocks back, the largest first, until at most `most` bytes stay.
+// Gives kept blocks back until at most `most` bytes in kKeptBlocks blocks
+// stay: those that are larger by themselves, then the longest kept, so that
+// what a repeated call has just freed is there for the next one.
 void trim_kept(size_t most) {
-    size_t sum = 0;
-    for (const Block& b : g_kept) sum += b.bytes;
-    while (sum > most && !g_kept.empty()) {
-        auto big = std::max_element(g_kept.begin(), g_kept.end(), [](const Block& a, const Block& b) { return a.bytes < b.bytes; });
-        (void)hipFree(big->p);
-        sum -= big->bytes;
-        g_kept.erase(big);
+    size_t sum = 0, n = g_kept.size();
+    for (Block& b : g_kept)
+        if (b.bytes > most) {
+            (void)hipFree(b.p);
+            b.p = nullptr;
+            --n;
+        } else {
+            sum += b.bytes;
+        }
+    for (Block& b : g_kept) {
+        if (sum <= most && n <= kKeptBlocks) break;
+        if (!b.p) continue;
+        (void)hipFree(b.p);
+        b.p = nullptr;
+        sum -= b.bytes;
+        --n;
     }
+    g_kept.erase(std::remove_if(g_kept.begin(), g_kept.end(), [](const Block& b) { return !b.p; }), g_kept.end());
 }
 
 // hipMemGetInfo with the kept blocks of this device counted as free.
 hipError_t free_memory(size_t* fr, size_t* total = nullptr) {
     size_t tot = 0;
     const hipError_t e = hipMemGetInfo(fr, &tot);
+    const int dev = this_device();
     if (e == hipSuccess)
         for (const Block& b : g_kept)
-            if (b.dev == this_device()) *fr += b.bytes;
+            if (b.dev == dev) *fr += b.bytes;
     if (total) *total = tot;
     return e;
 }

@@ -18,6 +18,7 @@ int g_dev = 0;
 size_t g_total = 0, g_others[kDevices];
 bool g_busy[kDevices];
 uintptr_t g_next = 1 << 20;
+int g_mallocs = 0;
 std::map<uintptr_t, std::pair<int, size_t>> g_blocks;
 
 size_t live(int dev) {
@@ -43,6 +44,8 @@ void fake_reset(long long total) {
 }
 void fake_others(int dev, long long bytes) { g_others[dev] = (size_t)bytes; }
 long long fake_live(int dev) { return (long long)live(dev); }
+int fake_blocks() { return (int)g_blocks.size(); }
+int fake_mallocs() { return g_mallocs; }
 int fake_busy(int dev) { return g_busy[dev]; }
 
 hipError_t hipGetDevice(int* d) { return *d = g_dev, hipSuccess; }
@@ -50,6 +53,7 @@ hipError_t hipSetDevice(int d) { return g_dev = d, hipSuccess; }
 hipError_t hipMemGetInfo(size_t* fr, size_t* tot) { return *fr = unused(g_dev), *tot = g_total, hipSuccess; }
 hipError_t hipMalloc(void** p, size_t bytes) {
     if (bytes > unused(g_dev)) return hipErrorOutOfMemory;
+    ++g_mallocs;
     *p = (void*)g_next;
     g_blocks[g_next] = {g_dev, bytes};
     g_next += (bytes + 511) / 256 * 256;

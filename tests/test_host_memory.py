@@ -96,3 +96,34 @@ def test_a_context_holds_no_medium_after_its_tables(host, prec, tables):
     finally:
         host.pm_set_precision(0)
         host.pm_finalize()
+
+
+def test_the_latest_blocks_stay(host):
+    """A program that differentiates over and over takes the same pool again,
+    also when older blocks of other sizes had filled the library's share."""
+    host.fake_reset(288 * GB)
+    grad = np.zeros(CELLS).ctypes.data_as(ctypes.POINTER(ctypes.c_double))
+    try:
+        _init(host)
+        assert host.pm_set_checkpoint(1) == 0 and host.pm_step(32) == 0
+        _init(host, edge=112)         # 32 states of 268 MB are left: the share is full
+        assert host.pm_set_checkpoint(4) == 0 and host.pm_step(8) == 0
+        assert host.pm_grad(grad, None, None) == 0
+        before = host.fake_mallocs()
+        for _ in range(3):
+            assert host.pm_grad(grad, None, None) == 0
+        assert host.fake_mallocs() == before
+    finally:
+        host.pm_finalize()
+
+
+def test_kept_blocks_are_few(host):
+    """Contexts of ever new sizes do not leave a growing list of small blocks."""
+    host.fake_reset(288 * GB)
+    try:
+        for nz in range(1, 300):
+            p = FIELD.ctypes.data_as(ctypes.POINTER(ctypes.c_double))
+            assert host.pm_init(N, 8, 8, 12 * nz, 0.1, 0.05, p, p, None) == 0
+        assert host.fake_blocks() <= 256 + 20
+    finally:
+        host.pm_finalize()
