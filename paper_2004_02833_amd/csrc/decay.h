@@ -15,13 +15,13 @@ __device__ __forceinline__ double dbeta_series(double z, double tau) {
 // dL/dc of a coefficient with decay factors al, be over tau, from
 // A = sum w u and B = sum w u' (w = be lam): lam u dal/dc + lam r dbe/dc,
 // with c recovered from the factors, c = (1 - al) / be.  be = 0 is an opaque
-// point (the mean of its cells' coefficients overflows): w = 0 and the
-// derivative is 0, where the quotients below would be 0 / 0.
+// point (the mean of its cells' coefficients overflows): al, A and B are 0 and
+// so is the derivative, where the quotients by be would be 0 / 0.
 __device__ __forceinline__ double dl_dc(double A, double B, double al, double be, double tau) {
-    if (be == 0.0) return 0.0;
     const double om = 1.0 - al;
     const double db = om < 1e-2 ? dbeta_series(tau * om / be, tau) : (tau * al - be) * be / om;
-    return ((B - al * A) * (db / be) - tau * al * A) / be;
+    const double d = be == 0.0 ? 1.0 : be;
+    return ((B - al * A) * (db / d) - tau * al * A) / d;
 }
 
 }  // namespace pm
