@@ -1,6 +1,7 @@
 // HIP kernels of libpm for gfx950 (MI355X): the window sweep, tables, halo
-// faces, reductions, gradient sums and conversions.  FP64 and FP32 isotropic
-// contexts of most sizes run the tile sweep or the low-order sweep instead.
+// faces, reductions, gradient sums and conversions.  Most isotropic contexts
+// run the low-order sweep or (FP64, FP32) the tile sweep instead; anisotropic
+// ones, BF16 above P6 to P9, small grids and P0 run the window sweep.
 //
 // State layout in HBM: moment-major planes, u[slot][z][y][x] with x fastest;
 // slots are grouped by staggered grid (G111, G221, G212, G122 | G211, G121,
